@@ -67,11 +67,11 @@ def parse():
 
 # Kernel (rocprofv3 name pattern) and source files behind each timed class.
 CLASS_KERNEL = {
-    "gemm_dense": (r"gemm_bf16_dense<[^>]*, 0>\(", ["gemm.hip", "gemm.h", "common.h"]),
-    "gemm_skinny": (r"gemm_bf16_skinny<", ["gemm.hip", "gemm.h", "common.h"]),
+    "gemm_dense": (r"gemm_bf16_dense<[^>]*, 0>\(", ["gemm.hip", "gemm_tile.h", "gemm.h", "common.h"]),
+    "gemm_skinny": (r"gemm_bf16_skinny<", ["gemm.hip", "gemm_tile.h", "gemm.h", "common.h"]),
     "attention": (r"attn_split<", ["attention.hip", "attention.h", "common.h"]),
     "attn_combine": (r"attn_combine<", ["attention.hip", "attention.h", "common.h"]),
-    "splitk_reduce": (r"splitk_reduce_kernel", ["gemm.hip", "gemm.h", "common.h"]),
+    "splitk_reduce": (r"splitk_reduce_kernel", ["gemm.hip", "gemm_tile.h", "gemm.h", "common.h"]),
 }
 TRAFFIC_TAG = "<!-- traffic "
 # Kernels whose HBM rate the profile summary reports against the peak: the
@@ -80,9 +80,8 @@ TRAFFIC_TAG = "<!-- traffic "
 HBM_RATE_KERNELS = [
     ("rollout attention (draft, hd 64, key groups)", r"attn_split<64, "),
     ("verification attention (target, hd 128)", r"attn_split<128, "),
-    ("rollout projections, 16 columns per wave, ring 8 (gate/up)", r"gemm_bf16_skinny<\d+, 1, 8, "),
-    ("rollout projections, 16 columns per wave, ring 4 (q/k/v, o, down)", r"gemm_bf16_skinny<\d+, 1, 4, "),
-    ("rollout LM head, 32 columns per wave", r"gemm_bf16_skinny<\d+, 2, 4, "),
+    ("rollout projections (q/k/v, o, gate/up, down)", r"gemm_bf16_skinny<[^>]*, 0, true, 0>"),
+    ("rollout LM head with its row statistics", r"gemm_bf16_skinny<[^>]*, 1, true, 0>"),
 ]
 
 

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <stdint.h>
 
 #include "common.h"
 
@@ -56,31 +57,34 @@ struct GemmOut {
 //                 *rs (RowStats in common.h), whose tiles field the launch
 //                 sets.  The K dimension is never split for it.
 //   kEpiRope:     no C; see RopeEpi (*rope).  Only where gemm_rope_fusable
-//                 holds: the dense kernel with no K split, whose output tile
-//                 holds whole heads.
-size_t gemm_workspace_bytes(int M, int N, int K, int dtype);
+//                 holds: no K split, and an output tile that holds whole
+//                 heads.
+// deferred: the split planes are left to the caller (see gemm_launch).
+size_t gemm_workspace_bytes(int M, int N, int K, int dtype, bool deferred = false);
 int gemm_check(int M, int N, int K, int dtype);
-// 0: dense bf16 kernel, 1: skinny bf16 kernel, 2: fp32 kernel
+// 0: bf16, more than 128 rows; 1: bf16, at most 128 rows; 2: fp32
 int gemm_kind(int M, int N, int K, int dtype);
 // Column tiles of a kEpiRowStats launch of this shape (0: not supported).
 int gemm_rowstats_tiles(int M, int N, int K, int dtype);
-// Whether a kEpiRope launch of this shape and head size is supported.
+// Whether a kEpiRope launch of this shape and head size is supported, and
+// cheaper than a projection and a rotary launch.
 bool gemm_rope_fusable(int M, int N, int K, int dtype, int hd);
 // Called between the main kernel and the split-K reduce, when there is one
 // (lets the caller time the two kernels separately).
 struct GemmHook {
   virtual void before_reduce(int ksplit) = 0;
 };
-// prefill selects a separately named instantiation of the dense kernel.
+// prefill selects a separately named instantiation of the kernel.
 // With deferred != null, a K split is left unreduced: the ksplit fp32
 // planes [ksplit][M][N] stay at the start of ws for the caller to consume
 // (before the next projection), the epilogue is not applied, and *deferred
 // receives ksplit (1: no split, the epilogue was applied as usual).
-// kEpiSwiGLU is never deferred.
+// kEpiSwiGLU is never deferred.  max_ws bounds the split planes that the
+// plan may ask for (a smaller split is taken instead).
 hipError_t gemm_launch(const GemmOperand& A, const void* B, const GemmOut& out, int M, int N, int K, int dtype,
                        int epi, void* ws, size_t ws_bytes, hipStream_t st, bool prefill = false,
                        GemmHook* hook = nullptr, int* deferred = nullptr, RowStats* rs = nullptr,
-                       const RopeEpi* rope = nullptr);
+                       const RopeEpi* rope = nullptr, size_t max_ws = SIZE_MAX);
 hipError_t swiglu_f32_launch(const float* gu, float* act, int M, int F, hipStream_t st);
 hipError_t split_planes_launch(const float* x, bf16* hi, bf16* lo, long long n, hipStream_t st);
 

@@ -1,0 +1,14 @@
+// bf16 projection kernels of passes of more than 128 rows.
+#include "gemm_tile.h"
+
+#define CASE(I, E, WM, WN, ...)                                                         \
+  case I * 3 + E:                                                                       \
+    gemm_bf16_dense<WM, WN, __VA_ARGS__, E, true, 0><<<grid, 64 * WM * WN, 0, st>>>(a);  \
+    break;
+#define CDSL_GEMM_CASE(I, ...) CASE(I, 0, __VA_ARGS__) CASE(I, 1, __VA_ARGS__) CASE(I, 2, __VA_ARGS__)
+
+namespace cdsl {
+
+CDSL_GEMM_KERNELS(gemm_bf16_dense, gemm_dense_kernels)
+
+}  // namespace cdsl

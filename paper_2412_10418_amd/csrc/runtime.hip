@@ -436,7 +436,7 @@ void alloc_workspace(cdsl_ctx* c) {
   }
   w.logits = dev_alloc<float>(c, (size_t)w.Mlog * Vm);
   for (auto& md : c->m)
-    for (int mm = 1; mm <= w.Mlog; ++mm)
+    for (int mm = 16; mm < w.Mlog + 16; mm += 16)   // row counts of one 16-row tile count share a plan
       w.rs_cap = std::max(w.rs_cap, (size_t)mm * gemm_rowstats_tiles(mm, md.c.vocab, md.c.d_model, c->dtype));
   w.rs_mx = dev_alloc<float>(c, w.rs_cap);
   w.rs_se = dev_alloc<float>(c, w.rs_cap);
@@ -455,8 +455,10 @@ void alloc_workspace(cdsl_ctx* c) {
   for (auto& md : c->m) {
     const int D = md.c.d_model, F = md.c.ffn_dim, V = md.c.vocab, HQ = md.c.n_heads * md.hd;
     const int shapes[5][2] = {{md.qkv_n, D}, {D, HQ}, {2 * F, D}, {D, F}, {V, D}};
-    for (int mm = 1; mm <= w.Mmax; ++mm)
-      for (auto& s : shapes) need = std::max(need, gemm_workspace_bytes(mm, s[0], s[1], c->dtype));
+    for (int mm = 16; mm < w.Mmax + 16; mm += 16)
+      for (auto& s : shapes)
+        need = std::max({need, gemm_workspace_bytes(mm, s[0], s[1], c->dtype, true),
+                         gemm_workspace_bytes(mm, s[0], s[1], c->dtype, false)});
   }
   w.gemm_ws_bytes = need;
   if (need) {
@@ -471,7 +473,8 @@ void alloc_workspace(cdsl_ctx* c) {
 // Returns the number of split planes left in the GEMM workspace for the
 // caller to fold (1: none) when defer is set.
 int gemm(cdsl_ctx* c, const GemmOperand& A, const void* W, const GemmOut& out, int M, int N, int K, int epi,
-         bool prefill, bool defer = false, RowStats* rs = nullptr, const RopeEpi* rope = nullptr) {
+         bool prefill, bool defer = false, RowStats* rs = nullptr, const RopeEpi* rope = nullptr,
+         bool no_split = false) {
   const double wes = c->dtype == CDSL_BF16 ? 2.0 : 4.0;   // weight element size
   // output bytes: fp32 store (also the rotary epilogue's fp32 q and hi / lo
   // K, V), fp32 read-modify-write, the two bf16 planes of the half-width
@@ -506,7 +509,7 @@ int gemm(cdsl_ctx* c, const GemmOperand& A, const void* W, const GemmOut& out, i
   hk.plane = (double)M * N * 4.0;
   int planes = 1;
   CK(gemm_launch(A, W, out, M, N, K, c->dtype, epi, c->ws.gemm_ws, c->ws.gemm_ws_bytes, c->st, prefill,
-                 c->prof ? &hk : nullptr, defer ? &planes : nullptr, rs, rope));
+                 c->prof ? &hk : nullptr, defer ? &planes : nullptr, rs, rope, no_split ? 0 : c->ws.gemm_ws_bytes));
   return planes;
 }
 
@@ -579,14 +582,14 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
   // consumes the result (RMSNorm of the residual stream, rotary + KV
   // write), which saves a reduce launch per projection.
   const float* planes_ws = (const float*)w.gemm_ws;
-  // Where the q/k/v projection is not split (the dense kernel at the
-  // verification and prefill row counts), its epilogue applies the rotary
-  // embedding and writes q and the KV pool itself: no q/k/v product in
-  // memory and no rotary launch.  CDSL_UNFUSED_ROPE=1 keeps the separate
-  // kernel (same arithmetic, for comparison).
+  // Where the q/k/v projection is best not split (gemm_rope_fusable), its
+  // epilogue applies the rotary embedding and writes q and the KV pool
+  // itself: no q/k/v product in memory and no rotary launch.
+  // CDSL_UNFUSED_ROPE=1 keeps the separate kernel after an unsplit
+  // projection (same arithmetic, for comparison).
   const char* unfused_env = getenv("CDSL_UNFUSED_ROPE");
-  const bool fuse_rope = bf && !(unfused_env && unfused_env[0] == '1') &&
-                         gemm_rope_fusable(M, md.qkv_n, D, c->dtype, hd);
+  const bool rope_fits = bf && gemm_rope_fusable(M, md.qkv_n, D, c->dtype, hd);
+  const bool fuse_rope = rope_fits && !(unfused_env && unfused_env[0] == '1');
   RopeEpi rope{p, w.rowinfo, w.q, md.pool, 0, md.cos_t, md.sin_t, H, Hkv, hd};
   {
     Span sp(c, CDSL_K_ROWWISE, 0.0, norm_bytes);
@@ -597,7 +600,8 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
       rope.layer = l;
       gemm(c, Au, md.wqkv[l], GemmOut{}, M, md.qkv_n, D, kEpiRope, prefill, false, nullptr, &rope);
     } else {
-      const int sq = gemm(c, Au, md.wqkv[l], to_qkv, M, md.qkv_n, D, kEpiStore, prefill, bf);
+      const int sq = gemm(c, Au, md.wqkv[l], to_qkv, M, md.qkv_n, D, kEpiStore, prefill, bf, nullptr, nullptr,
+                          rope_fits);
       Span sp(c, CDSL_K_ROWWISE, 0.0, rope_bytes + (sq > 1 ? (double)sq * M * md.qkv_n * 4.0 : 0.0));
       CK(rope_kv_launch(p, sq > 1 ? planes_ws : w.qkv, w.q, md.pool, l, md.cos_t, md.sin_t, H, Hkv, hd, dt, c->st,
                         sq > 1 ? sq : 0));
@@ -1654,14 +1658,10 @@ size_t cdsl_op_gemm_workspace(int32_t M, int32_t N, int32_t K, int32_t dtype) {
   return op_planes_bytes(M, K, dtype) + gemm_workspace_bytes(M, N, K, dtype);
 }
 
-int cdsl_op_gemm(const void* A, const void* B, float* C, int32_t M, int32_t N, int32_t K, int32_t dtype,
-                 int32_t epilogue, void* workspace, size_t workspace_bytes, void* stream) {
-  if (!A || !B || !C) return fail(nullptr, CDSL_EINVAL, "null argument");
-  if (dtype != CDSL_F32 && dtype != CDSL_BF16) return fail(nullptr, CDSL_EINVAL, "bad dtype");
-  if (epilogue != CDSL_EPI_STORE && epilogue != CDSL_EPI_RESIDUAL) return fail(nullptr, CDSL_EINVAL, "bad epilogue");
-  if (gemm_check(M, N, K, dtype) != 0) return fail(nullptr, CDSL_EINVAL, "unsupported shape");
-  if (cdsl_op_gemm_workspace(M, N, K, dtype) > workspace_bytes)
-    return fail(nullptr, CDSL_EINVAL, "workspace too small");
+namespace {
+// max_split: the most that the split-K planes may take
+int op_gemm(const void* A, const void* B, float* C, int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epilogue,
+            void* workspace, size_t workspace_bytes, void* stream, size_t max_split) {
   if (M == 0) return CDSL_OK;
   hipStream_t st = (hipStream_t)stream;
   GemmOperand op{nullptr, nullptr, (const float*)A};
@@ -1674,9 +1674,65 @@ int cdsl_op_gemm(const void* A, const void* B, float* C, int32_t M, int32_t N, i
     op = GemmOperand{hi, lo, nullptr};
   }
   hipError_t e = gemm_launch(op, B, GemmOut{C, nullptr, nullptr, N}, M, N, K, dtype, epilogue,
-                             (char*)workspace + pb, workspace_bytes - pb, st);
+                             (char*)workspace + pb, workspace_bytes - pb, st, false, nullptr, nullptr, nullptr,
+                             nullptr, max_split);
   if (e != hipSuccess) return fail(nullptr, CDSL_EDEVICE, hipGetErrorString(e));
   return CDSL_OK;
+}
+
+// The bytes that cdsl_op_gemm_static's limit is about: the planes of A and
+// those of a K split that fills the chip with tiles of 160 x 256 (more than
+// 128 rows) or of 64 or 128 columns.  It says which shapes are taken; the
+// split that runs is the plan's, within the scratch.
+size_t static_need(int M, int N, int K, int dtype) {
+  if (M <= 0 || N <= 0 || K <= 0) return 0;
+  if (dtype != CDSL_BF16) return 0;
+  int s = 1;
+  if (M <= 128 && K % 64 == 0) {
+    const int nst = K / 64;
+    const bool wide = (N + 63) / 64 >= 200, two = wide && (N + 127) / 128 >= 200;
+    const int ring = wide && !two ? 8 : 4, tiles = two ? (N + 127) / 128 : (N + 63) / 64;
+    s = std::max(1, std::min(wide ? 1 : (256 + tiles - 1) / tiles, nst / ring));
+    int per = (nst + s - 1) / s;
+    if (nst >= ring) per = (per + ring - 1) / ring * ring;
+    s = (nst + per - 1) / per;
+  } else {
+    const int tiles = ((M + 159) / 160) * ((N + 255) / 256), nk = K / (K % 64 ? 32 : 64);
+    double best = 1e300;
+    for (int c = 1; c <= 32 && c <= std::max(1, nk / 2); ++c) {
+      const int per = (nk + c - 1) / c;
+      const double rounds = (double)((tiles * c + 255) / 256);
+      const double planes = c > 1 ? (c + 1.0) * M * N * 4.0 / 5e12 / 2e-6 : 0.0;
+      const double t = (rounds * (per + 2.0) + planes) * (c > 1 ? 1.05 : 1.0);
+      if (t < best - 1e-9) {
+        best = t;
+        s = c;
+      }
+    }
+    const int per = (nk + s - 1) / s;
+    s = (nk + per - 1) / per;
+  }
+  const size_t split = s > 1 ? ((size_t)s * M * N * sizeof(float) + 255) & ~(size_t)255 : 0;
+  return op_planes_bytes(M, K, dtype) + split;
+}
+
+int op_gemm_check(const void* A, const void* B, const float* C, int32_t M, int32_t N, int32_t K, int32_t dtype,
+                  int32_t epilogue) {
+  if (!A || !B || !C) return fail(nullptr, CDSL_EINVAL, "null argument");
+  if (dtype != CDSL_F32 && dtype != CDSL_BF16) return fail(nullptr, CDSL_EINVAL, "bad dtype");
+  if (epilogue != CDSL_EPI_STORE && epilogue != CDSL_EPI_RESIDUAL) return fail(nullptr, CDSL_EINVAL, "bad epilogue");
+  if (gemm_check(M, N, K, dtype) != 0) return fail(nullptr, CDSL_EINVAL, "unsupported shape");
+  return CDSL_OK;
+}
+}  // namespace
+
+int cdsl_op_gemm(const void* A, const void* B, float* C, int32_t M, int32_t N, int32_t K, int32_t dtype,
+                 int32_t epilogue, void* workspace, size_t workspace_bytes, void* stream) {
+  const int rc = op_gemm_check(A, B, C, M, N, K, dtype, epilogue);
+  if (rc != CDSL_OK) return rc;
+  if (cdsl_op_gemm_workspace(M, N, K, dtype) > workspace_bytes)
+    return fail(nullptr, CDSL_EINVAL, "workspace too small");
+  return op_gemm(A, B, C, M, N, K, dtype, epilogue, workspace, workspace_bytes, stream, SIZE_MAX);
 }
 
 }  // extern "C"
@@ -1695,10 +1751,9 @@ extern "C" {
 
 int cdsl_op_gemm_static(const void* A, const void* B, float* C, int32_t M, int32_t N, int32_t K, int32_t dtype,
                         int32_t epilogue, void* stream) {
-  if (!A || !B || !C) return fail(nullptr, CDSL_EINVAL, "null argument");
-  if (dtype != CDSL_F32 && dtype != CDSL_BF16) return fail(nullptr, CDSL_EINVAL, "bad dtype");
-  if (gemm_check(M, N, K, dtype) != 0) return fail(nullptr, CDSL_EINVAL, "unsupported shape");
-  const size_t need = cdsl_op_gemm_workspace(M, N, K, dtype);
+  const int rc = op_gemm_check(A, B, C, M, N, K, dtype, epilogue);
+  if (rc != CDSL_OK) return rc;
+  const size_t need = static_need(M, N, K, dtype);
   if (need > CDSL_OP_GEMM_STATIC_BYTES)
     return fail(nullptr, CDSL_ERANGE,
                 "shape needs " + std::to_string(need) + " bytes of workspace; the static scratch holds " +
@@ -1718,7 +1773,8 @@ int cdsl_op_gemm_static(const void* A, const void* B, float* C, int32_t M, int32
     }
     ws = g_scratch_dev[dev];
   }
-  return cdsl_op_gemm(A, B, C, M, N, K, dtype, epilogue, ws, CDSL_OP_GEMM_STATIC_BYTES, stream);
+  return op_gemm(A, B, C, M, N, K, dtype, epilogue, ws, CDSL_OP_GEMM_STATIC_BYTES, stream,
+                 CDSL_OP_GEMM_STATIC_BYTES - op_planes_bytes(M, K, dtype));
 }
 
 int cdsl_op_logit_rows(const float* logits, int32_t M, int32_t V, const int32_t* gather, int32_t kk, float* lp,
