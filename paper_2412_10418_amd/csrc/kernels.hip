@@ -323,166 +323,210 @@ __global__ __launch_bounds__(NT) void rope_kv_write_split(PassDesc p, const floa
 }
 
 // ---------------------------------------------------------------------------
-// Logits row statistics, one workgroup per row, one read of the row:
-// online logsumexp, argmax, thread-local top-KK lists merged by KK rounds of
-// block argmax.  Ordering: value descending, then id ascending.
 // A token id that indexes the vocabulary even for a row without a finite
 // logit (all NaN), so that the next pass's embedding never reads out of
 // bounds; the NaN still reaches the scores and makes the selection fail.
 __device__ __forceinline__ int vocab_id(int id, int V) { return (id >= 0 && id < V) ? id : 0; }
 
-template <int KKMAX>
-__global__ __launch_bounds__(256) void logit_rows_kernel(LogitArgs a) {
-  __shared__ float shv[4];
-  __shared__ int shi[4];
-  __shared__ float shs[4];
-  const int m = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const float* z = a.logits + (long long)m * (a.ld ? a.ld : (long long)a.V);
-
-  float mloc = -INFINITY, sloc = 0.f;
-  float bv = -INFINITY;
-  int bid = 0x7fffffff;
-  float lv[KKMAX > 0 ? KKMAX : 1];
-  int li[KKMAX > 0 ? KKMAX : 1];
+// A row of V floats read as 16-byte slots: slot q holds ids 4q - shift .. + 3,
+// shift chosen so that the slots are aligned whatever V and the row are.  Ids
+// outside the row read as -inf.
+struct RowSlots {
+  const float* z;
+  int V, shift, slots;
+  bool vec;   // the slots of this row are 16-byte aligned
+  __device__ __forceinline__ void load(int q, float (&x)[4]) const {
+    const int id = 4 * q - shift;
+    if (vec && id >= 0 && id + 4 <= V) {
+      const float4 v = *(const float4*)(z + id);
+      x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+    } else {
 #pragma unroll
-  for (int s = 0; s < (KKMAX > 0 ? KKMAX : 1); ++s) {
-    lv[s] = -INFINITY;
-    li[s] = 0x7fffffff;
+      for (int e = 0; e < 4; ++e) x[e] = id + e >= 0 && id + e < V ? z[id + e] : -INFINITY;
+    }
   }
-  auto visit = [&](float v, int id) {
-    if (a.want_lse) {
-      if (v > mloc) {
-        sloc = sloc * __expf(mloc - v) + 1.f;
-        mloc = v;
-      } else {
-        sloc += __expf(v - mloc);
-      }
-    }
-    if (vi_better(v, id, bv, bid)) {
-      bv = v;
-      bid = id;
-    }
-    // keep the best KKMAX (>= kk) so every list index is static
-    if (KKMAX > 0 && vi_better(v, id, lv[(KKMAX > 0 ? KKMAX : 1) - 1], li[(KKMAX > 0 ? KKMAX : 1) - 1])) {
-      float cv = v;
-      int ci = id;
+};
+__device__ __forceinline__ RowSlots row_slots(const float* z, int V, int shift) {
+  return {z, V, shift, (V + shift + 3) / 4, ((uintptr_t)z / 4 & 3) == (unsigned)shift};
+}
+
+constexpr float kLog2e = 1.4426950408889634f;
+
+// Adds N values to a running (maximum m, sum s of exp(v - m)).  A chunk's own
+// maximum is taken first, so s is scaled at most once per chunk; a NaN among
+// the values makes s NaN.
+template <int N>
+__device__ __forceinline__ void lse_add(const float (&x)[N], float cm, float& m, float& s) {
+  const float mn = fmaxf(m, cm);
+  if (mn == -INFINITY) {
 #pragma unroll
-      for (int s = 0; s < KKMAX; ++s) {
-        if (vi_better(cv, ci, lv[s], li[s])) {
-          float tv = lv[s];
-          int ti = li[s];
-          lv[s] = cv;
-          li[s] = ci;
-          cv = tv;
-          ci = ti;
-        }
-      }
+    for (int e = 0; e < N; ++e)
+      if (x[e] != x[e]) s = x[e];
+    return;
+  }
+  s *= __builtin_amdgcn_exp2f((m - mn) * kLog2e);   // m = -inf: 0
+  m = mn;
+#pragma unroll
+  for (int e = 0; e < N; ++e) s += __builtin_amdgcn_exp2f((x[e] - mn) * kLog2e);
+}
+
+// the logsumexp of a workgroup's (m, s); every thread returns it
+template <int NW>
+__device__ __forceinline__ float block_lse(float m, float s, float (&sm)[NW], float (&ss)[NW]) {
+  const float wm = wave_max(m);
+  const float ws = wave_sum(wm == -INFINITY ? s : s * __builtin_amdgcn_exp2f((m - wm) * kLog2e));
+  if ((threadIdx.x & 63) == 0) {
+    sm[threadIdx.x >> 6] = wm;
+    ss[threadIdx.x >> 6] = ws;
+  }
+  __syncthreads();
+  float M = -INFINITY, t = 0.f;
+#pragma unroll
+  for (int u = 0; u < NW; ++u) M = fmaxf(M, sm[u]);
+#pragma unroll
+  for (int u = 0; u < NW; ++u) t += sm[u] == -INFINITY ? ss[u] : ss[u] * __builtin_amdgcn_exp2f((sm[u] - M) * kLog2e);
+  return M + __logf(t);
+}
+
+// Logits row statistics, one workgroup per row, one read of the row: online
+// logsumexp, argmax, top-kk.  Ordering: value descending, then id ascending.
+//
+// Bound by the read.  A thread keeps only the maximum of each of its GN
+// groups of columns (16 columns of every GN-th chunk); a place of the top-kk
+// is the best of the waves' bests, and only the wave that held it looks for
+// its next one: the lanes whose maximum is the wave's read that group again
+// (from L2) for the lowest id.  Before, every thread kept a sorted list of
+// the kk best: 512 rows of 50257, top-5, took 157 us.
+constexpr int kRowGroups = 8;
+
+template <int NT, bool LSE>
+__global__ __launch_bounds__(NT) void logit_rows_kernel(LogitArgs a) {
+  constexpr int NW = NT / 64, GN = kRowGroups;
+  __shared__ float sv[2][NW], sm[NW], ss[NW];
+  __shared__ int si[2][NW];
+  const int row = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const float* z = a.logits + (long long)row * (a.ld ? a.ld : (long long)a.V);
+  const RowSlots rs = row_slots(z, a.V, (int)((uintptr_t)z / 4 & 3));
+  const int nc = (rs.slots + 4 * NT - 1) / (4 * NT);   // chunks of 4 slots per thread
+  auto chunk = [&](int c, float (&x)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float t[4];
+      rs.load(tid + NT * (4 * c + i), t);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[4 * i + e] = t[e];
     }
   };
-  const int V4 = (a.V & 3) == 0 ? a.V / 4 : 0;
-  const float4* z4 = (const float4*)z;
-  for (int c = tid; c < V4; c += 256) {
-    float4 v = z4[c];
-    visit(v.x, 4 * c);
-    visit(v.y, 4 * c + 1);
-    visit(v.z, 4 * c + 2);
-    visit(v.w, 4 * c + 3);
-  }
-  for (int c = 4 * V4 + tid; c < a.V; c += 256) visit(z[c], c);
+  auto id_of = [&](int c, int e) { return 4 * (tid + NT * (4 * c + (e >> 2))) - rs.shift + (e & 3); };
 
-  // argmax
-  {
-    float v = bv;
-    int id = bid;
+  float g[GN], m = -INFINITY, s = 0.f;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      float ov = __shfl_xor(v, o, 64);
-      int oi = __shfl_xor(id, o, 64);
-      if (vi_better(ov, oi, v, id)) {
-        v = ov;
-        id = oi;
+  for (int u = 0; u < GN; ++u) g[u] = -INFINITY;
+  for (int c0 = 0; c0 < nc; c0 += GN) {
+#pragma unroll
+    for (int u = 0; u < GN; ++u) {
+      if (c0 + u >= nc) break;
+      float x[16];
+      chunk(c0 + u, x);
+      float cm = x[0];
+#pragma unroll
+      for (int e = 1; e < 16; ++e) cm = fmaxf(cm, x[e]);
+      cm = fmaxf(cm, -INFINITY);   // all NaN: -inf
+      g[u] = fmaxf(g[u], cm);
+      if (LSE) lse_add(x, cm, m, s);
+      else if (u & 1) __builtin_amdgcn_sched_barrier(0);   // two chunks' loads in flight per wave
+    }
+  }
+  // this wave's best entry ordered after (pv, pi), which no entry outside the
+  // groups' maxima precedes
+  auto wave_best = [&](float pv, int pi, float& wv, int& wi) {
+    float tv = g[0];
+#pragma unroll
+    for (int u = 1; u < GN; ++u) tv = fmaxf(tv, g[u]);
+    wv = wave_max(tv);
+    int id = 0x7fffffff;
+    if (tv == wv) {
+#pragma unroll 1
+      for (int c = 0; c < nc; ++c) {
+        float gu = g[0];
+#pragma unroll
+        for (int u = 1; u < GN; ++u) gu = (c & (GN - 1)) == u ? g[u] : gu;
+        if (gu != wv) continue;
+        float x[16];
+        chunk(c, x);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int t = id_of(c, e);
+          if (x[e] == wv && t >= 0 && t < a.V && (wv < pv || t > pi)) id = min(id, t);
+        }
       }
     }
-    if (lane == 0) {
-      shv[w] = v;
-      shi[w] = id;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      float fv = shv[0];
-      int fi = shi[0];
-      for (int u = 1; u < 4; ++u)
-        if (vi_better(shv[u], shi[u], fv, fi)) {
-          fv = shv[u];
-          fi = shi[u];
-        }
-      shi[0] = fi;
-      shv[0] = fv;
-    }
-    __syncthreads();
-    if (tid == 0 && a.amax) a.amax[rowmap_index(a.amax_map, m)] = vocab_id(shi[0], a.V);
-    __syncthreads();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) id = min(id, __shfl_xor(id, o, 64));
+    wi = id;
+  };
+  // the best of the waves' bests in buffer b
+  auto block_best = [&](int b, float& bv, int& bi) {
+    bv = sv[b][0];
+    bi = si[b][0];
+#pragma unroll
+    for (int u = 1; u < NW; ++u)
+      if (vi_better(sv[b][u], si[b][u], bv, bi)) {
+        bv = sv[b][u];
+        bi = si[b][u];
+      }
+  };
+  float wv;
+  int wi;
+  wave_best(INFINITY, -1, wv, wi);
+  if (lane == 0) {
+    sv[0][w] = wv;
+    si[0][w] = wi;
   }
-  if (!a.want_lse) return;
-  // logsumexp
-  float lse;
-  {
-    float mm = wave_max(mloc);
-    if (lane == 0) shv[w] = mm;
-    __syncthreads();
-    const float M = fmaxf(fmaxf(shv[0], shv[1]), fmaxf(shv[2], shv[3]));
-    float sv = mloc == -INFINITY ? 0.f : sloc * __expf(mloc - M);
-    sv = wave_sum(sv);
-    if (lane == 0) shs[w] = sv;
-    __syncthreads();
-    lse = M + __logf(shs[0] + shs[1] + shs[2] + shs[3]);
-    __syncthreads();
-  }
+  float lse = 0.f;
+  if (LSE) lse = block_lse<NW>(m, s, sm, ss);
+  else __syncthreads();
+  float bv;
+  int bi;
+  block_best(0, bv, bi);
+  if (tid == 0 && a.amax) a.amax[rowmap_index(a.amax_map, row)] = vocab_id(bi, a.V);
+  if (!LSE) return;
   if (a.lp && tid == 0) {
-    const int tok = a.gather_tok[rowmap_index(a.gather_map, m)];
+    const int tok = a.gather_tok[rowmap_index(a.gather_map, row)];
     const bool in = tok >= 0 && tok < a.V;
     if (!in && a.bad) *a.bad = 1;
-    a.lp[m] = in ? z[tok] - lse : __int_as_float(0x7fc00000);
+    a.lp[row] = in ? z[tok] - lse : __int_as_float(0x7fc00000);
   }
-  if (KKMAX == 0 || a.kk == 0) return;
-  const int dst = a.topk_rows ? a.topk_rows[m] : m;
+  if (a.kk == 0) return;
+  const int dst = a.topk_rows ? a.topk_rows[row] : row;
   for (int r = 0; r < a.kk; ++r) {
-    float v = lv[0];
-    int id = li[0];
+    if (r > 0) block_best(r & 1, bv, bi);
+    if (tid == 0) {
+      a.topk_ids[(long long)dst * a.kk + r] = vocab_id(bi, a.V);
+      a.topk_lp[(long long)dst * a.kk + r] = bv - lse;
+    }
+    if (r + 1 == a.kk) break;
+    if (wi == bi && bi != 0x7fffffff) {   // this wave held it (uniform)
+      const int q = (bi + rs.shift) >> 2, u0 = (q / (4 * NT)) & (GN - 1);
+      if (q % NT == tid) {
+        float gm = -INFINITY;
+#pragma unroll 1
+        for (int c = u0; c < nc; c += GN) {
+          float x[16];
+          chunk(c, x);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      float ov = __shfl_xor(v, o, 64);
-      int oi = __shfl_xor(id, o, 64);
-      if (vi_better(ov, oi, v, id)) {
-        v = ov;
-        id = oi;
+          for (int e = 0; e < 16; ++e)
+            if (x[e] < bv || (x[e] == bv && id_of(c, e) > bi && id_of(c, e) < a.V)) gm = fmaxf(gm, x[e]);
+        }
+#pragma unroll
+        for (int u = 0; u < GN; ++u) g[u] = u == u0 ? gm : g[u];
       }
+      wave_best(bv, bi, wv, wi);
     }
     if (lane == 0) {
-      shv[w] = v;
-      shi[w] = id;
-    }
-    __syncthreads();
-    float fv = shv[0];
-    int fi = shi[0];
-    for (int u = 1; u < 4; ++u)
-      if (vi_better(shv[u], shi[u], fv, fi)) {
-        fv = shv[u];
-        fi = shi[u];
-      }
-    if (tid == 0) {
-      a.topk_ids[(long long)dst * a.kk + r] = vocab_id(fi, a.V);
-      a.topk_lp[(long long)dst * a.kk + r] = fv - lse;
-    }
-    if (li[0] == fi) {   // ids are unique: exactly one thread pops
-#pragma unroll
-      for (int s = 0; s + 1 < (KKMAX > 0 ? KKMAX : 1); ++s) {
-        lv[s] = lv[s + 1];
-        li[s] = li[s + 1];
-      }
-      lv[(KKMAX > 0 ? KKMAX : 1) - 1] = -INFINITY;
-      li[(KKMAX > 0 ? KKMAX : 1) - 1] = 0x7fffffff;
+      sv[(r + 1) & 1][w] = wv;
+      si[(r + 1) & 1][w] = wi;
     }
     __syncthreads();
   }
@@ -554,150 +598,215 @@ __global__ void select_kernel(int B, int k, const float* __restrict__ scores, co
 //   res_ids[m]  = the draw at v[m] from w = max(0, p - q) / Z, inverting the
 //                 cumulative sum over token ids in ascending order (argmax p
 //                 when Z = 0), and res_lp[m] = log p of it.
-// Three passes over the rows: both logsumexps and argmax p; per-wave sums
-// of w over four contiguous id segments; one wave walks the segment that
-// holds v * Z with a 64-lane scan per chunk.
-__global__ __launch_bounds__(256) void soft_rows_kernel(const float* __restrict__ zp_all,
-                                                        const float* __restrict__ zq_all, int V, int d,
-                                                        const int* __restrict__ look, const float* __restrict__ v,
-                                                        float* __restrict__ draft_lp, int* __restrict__ res_ids,
-                                                        float* __restrict__ res_lp) {
-  __shared__ float sh_m[2][4], sh_s[2][4], sh_bv[4], part[4];
-  __shared__ int sh_bi[4];
-  __shared__ int sh_res;
-  const int m = blockIdx.x;
+//
+// Bound by the two reads of the two rows, from HBM and then from the caches
+// (holding both rows in the registers of 1024 threads leaves one workgroup per
+// CU, whose loads and sums then do not overlap: 91 against 78 us for 800 rows
+// of 32000; the floor of one read is 45 us).  Blocks of 4 NT consecutive ids
+// (f of them per segment) are summed per wave; the segment that holds v * Z,
+// then its block, its wave (256 consecutive ids) and a scan over that wave's
+// lanes find the draw.  Before, four waves walked a quarter of the row each,
+// 64 ids at a time: 219 us.
+template <int NT>
+__global__ __launch_bounds__(NT) void soft_rows_kernel(const float* __restrict__ zp_all,
+                                                       const float* __restrict__ zq_all, int V, int d,
+                                                       const int* __restrict__ look, const float* __restrict__ v,
+                                                       float* __restrict__ draft_lp, int* __restrict__ res_ids,
+                                                       float* __restrict__ res_lp) {
+  constexpr int NW = NT / 64, NSEG = 64;
+  __shared__ float sm[2][NW], ss[2][NW], part[NSEG][NW], seg[NSEG], wsum[NW];
+  __shared__ int sh_res, sh_arg[NW];
+  const int row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const float* zp = zp_all + (long long)m * V;
-  const float* zq = zq_all + (long long)m * V;
-
-  float mp = -INFINITY, sp = 0.f, mq = -INFINITY, sq = 0.f, bv = -INFINITY;
-  int bi = 0x7fffffff;
-  for (int t = tid; t < V; t += 256) {
-    const float a = zp[t], b = zq[t];
-    if (a > mp) {
-      sp = sp * __expf(mp - a) + 1.f;
-      mp = a;
-    } else {
-      sp += __expf(a - mp);
+  const float* zp = zp_all + (long long)row * V;
+  const float* zq = zq_all + (long long)row * V;
+  const int shift = (int)((uintptr_t)zp / 4 & 3);
+  const RowSlots rp = row_slots(zp, V, shift), rq = row_slots(zq, V, shift);
+  const int nb = (rp.slots + NT - 1) / NT;      // blocks of NT slots
+  const int f = (nb + NSEG - 1) / NSEG, ns = (nb + f - 1) / f;
+  float mp = -INFINITY, sp = 0.f, mq = -INFINITY, sq = 0.f;
+  for (int b0 = 0; b0 < nb; b0 += 4) {
+    float x[16], y[16];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float tx[4], ty[4];
+      rp.load(tid + NT * (b0 + u), tx);
+      rq.load(tid + NT * (b0 + u), ty);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[4 * u + e] = tx[e], y[4 * u + e] = ty[e];
     }
-    if (b > mq) {
-      sq = sq * __expf(mq - b) + 1.f;
-      mq = b;
-    } else {
-      sq += __expf(b - mq);
+    float cp = -INFINITY, cq = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      cp = fmaxf(cp, x[e]);
+      cq = fmaxf(cq, y[e]);
     }
-    if (vi_better(a, t, bv, bi)) {
-      bv = a;
-      bi = t;
+    lse_add(x, cp, mp, sp);
+    lse_add(y, cq, mq, sq);
+  }
+  const float lp = block_lse<NW>(mp, sp, sm[0], ss[0]);
+  const float lq = block_lse<NW>(mq, sq, sm[1], ss[1]);
+  // w of this thread's four ids of block b
+  auto weights = [&](const float (&x)[4], const float (&y)[4], float (&t)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      t[e] = fmaxf(0.f, __builtin_amdgcn_exp2f((x[e] - lp) * kLog2e) - __builtin_amdgcn_exp2f((y[e] - lq) * kLog2e));
+  };
+  auto block_weights = [&](int b, float (&t)[4]) __attribute__((always_inline)) {
+    float x[4], y[4];
+    rp.load(tid + NT * b, x);
+    rq.load(tid + NT * b, y);
+    weights(x, y, t);
+  };
+  if (f == 1) {   // four blocks' loads in flight
+    for (int b0 = 0; b0 < nb; b0 += 4) {
+      float x[4][4], y[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        rp.load(tid + NT * (b0 + u), x[u]);
+        rq.load(tid + NT * (b0 + u), y[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float t[4];
+        weights(x[u], y[u], t);
+        const float ws = wave_sum((t[0] + t[1]) + (t[2] + t[3]));
+        if (lane == 0 && b0 + u < nb) part[b0 + u][wv] = ws;
+      }
+    }
+  } else {
+    for (int g = 0; g < ns; ++g) {
+      float acc = 0.f;
+      for (int b = g * f; b < min(nb, g * f + f); ++b) {
+        float t[4];
+        block_weights(b, t);
+        acc += (t[0] + t[1]) + (t[2] + t[3]);
+      }
+      acc = wave_sum(acc);
+      if (lane == 0) part[g][wv] = acc;
     }
   }
-  {
-    float ov;
-    int oi;
+  if (tid == 0) sh_res = -1;
+  __syncthreads();
+  if (tid < ns) {
+    float t = 0.f;
+#pragma unroll
+    for (int u = 0; u < NW; ++u) t += part[tid][u];
+    seg[tid] = t;
+  }
+  __syncthreads();
+  float Z = 0.f;
+  for (int g = 0; g < ns; ++g) Z += seg[g];
+  const float T = v[row] * Z;
+  // the first entry of p[0..n) whose running sum passes T (the last one with
+  // mass when rounding leaves T past the total; -1: no mass); before: the sum
+  // in front of it
+  auto locate = [](const float* p, int n, float T, float& before) {
+    float run = 0.f;
+    int at = -1;
+    before = 0.f;
+    for (int u = 0; u < n; ++u) {
+      if (p[u] > 0.f) {
+        at = u;
+        before = run;
+        if (run + p[u] > T) break;
+      }
+      run += p[u];
+    }
+    return at;
+  };
+  float before;
+  const int sg = Z > 0.f ? locate(seg, ns, T, before) : -1;
+  if (sg >= 0) {   // uniform over the workgroup
+    float Tl = T - before;
+    for (int b = sg * f; b < min(nb, sg * f + f); ++b) {
+      float t[4];
+      block_weights(b, t);
+      const float mine = (t[0] + t[1]) + (t[2] + t[3]);
+      const float ws = wave_sum(mine);
+      __syncthreads();
+      if (lane == 0) wsum[wv] = ws;
+      __syncthreads();
+      float bs = 0.f, bw;
+#pragma unroll
+      for (int u = 0; u < NW; ++u) bs += wsum[u];
+      const int wl = bs > 0.f ? locate(wsum, NW, Tl, bw) : -1;
+      if (wl == wv) {
+        const float Tw = Tl - bw;
+        // inclusive scan over the lanes, then over a lane's four ids
+        float sc = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const float n = __shfl_up(sc, o, 64);
+          if (lane >= o) sc += n;
+        }
+        float run = __shfl_up(sc, 1, 64);
+        if (lane == 0) run = 0.f;
+        int hit = -1, last = -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (t[e] > 0.f) {
+            last = e;
+            if (hit < 0 && run + t[e] > Tw) hit = e;
+          }
+          run += t[e];
+        }
+        const unsigned long long hits = __ballot(hit >= 0), mass = __ballot(last >= 0);
+        const int from = hits ? __builtin_ctzll(hits) : 63 - __builtin_clzll(mass | 1ull);
+        if (lane == from && (hits || mass)) sh_res = 4 * (tid + NT * b) - shift + (hits ? hit : last);
+      }
+      // done when the draw's running sum was inside this block; a later block
+      // of the segment that holds mass takes over when rounding left T past it
+      if (bs > Tl) break;
+      Tl -= bs;
+    }
+  }
+  __syncthreads();
+  int res = sh_res;
+  if (res < 0) {   // no mass: the argmax of p, lowest id (uniform)
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int b = 0; b < nb; ++b) {
+      float x[4];
+      rp.load(tid + NT * b, x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int id = 4 * (tid + NT * b) - shift + e;
+        if (id >= 0 && id < V && vi_better(x[e], id, bv, bi)) {
+          bv = x[e];
+          bi = id;
+        }
+      }
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-      ov = __shfl_xor(bv, o, 64);
-      oi = __shfl_xor(bi, o, 64);
+      const float ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
       if (vi_better(ov, oi, bv, bi)) {
         bv = ov;
         bi = oi;
       }
     }
-    const float Mp = wave_max(mp), Mq = wave_max(mq);
-    const float s1 = wave_sum(mp == -INFINITY ? 0.f : sp * __expf(mp - Mp));
-    const float s2 = wave_sum(mq == -INFINITY ? 0.f : sq * __expf(mq - Mq));
     if (lane == 0) {
-      sh_m[0][wv] = Mp;
-      sh_s[0][wv] = s1;
-      sh_m[1][wv] = Mq;
-      sh_s[1][wv] = s2;
-      sh_bv[wv] = bv;
-      sh_bi[wv] = bi;
+      wsum[wv] = bv;
+      sh_arg[wv] = bi;
     }
-  }
-  __syncthreads();
-  float lse[2];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const float M = fmaxf(fmaxf(sh_m[r][0], sh_m[r][1]), fmaxf(sh_m[r][2], sh_m[r][3]));
-    float sum = 0.f;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) sum += sh_m[r][u] == -INFINITY ? 0.f : sh_s[r][u] * __expf(sh_m[r][u] - M);
-    lse[r] = M + __logf(sum);
-  }
-  int amax = sh_bi[0];
-  {
-    float av = sh_bv[0];
-    for (int u = 1; u < 4; ++u)
-      if (vi_better(sh_bv[u], sh_bi[u], av, amax)) {
-        av = sh_bv[u];
-        amax = sh_bi[u];
+    __syncthreads();
+    bv = wsum[0];
+    res = sh_arg[0];
+    for (int u = 1; u < NW; ++u)
+      if (vi_better(wsum[u], sh_arg[u], bv, res)) {
+        bv = wsum[u];
+        res = sh_arg[u];
       }
   }
-  // per-wave sums of w over contiguous segments (multiples of 64 ids)
-  const int seg = ((V + 255) / 256) * 64;
-  const int s0 = wv * seg, s1 = min(V, s0 + seg);
-  float acc = 0.f;
-  for (int t = s0 + lane; t < s1; t += 64) acc += fmaxf(0.f, __expf(zp[t] - lse[0]) - __expf(zq[t] - lse[1]));
-  acc = wave_sum(acc);
-  if (lane == 0) part[wv] = acc;
-  if (tid == 0) sh_res = -1;
-  __syncthreads();
-  const float Z = part[0] + part[1] + part[2] + part[3];
-  const float T = v[m] * Z;
-  // segment holding T (the last one with mass when rounding leaves T past the total)
-  int sg = -1;
-  float before = 0.f;
-  {
-    float run = 0.f;
-    for (int u = 0; u < 4; ++u) {
-      if (part[u] > 0.f) {
-        if (run + part[u] > T) {
-          sg = u;
-          before = run;
-          break;
-        }
-        sg = u;
-        before = run;
-      }
-      run += part[u];
-    }
-  }
-  if (Z > 0.f && wv == sg) {
-    const int g0 = sg * seg, g1 = min(V, g0 + seg);
-    const float Tl = T - before;
-    float run = 0.f;
-    int last = -1;
-    int found = -1;
-    for (int c0 = g0; c0 < g1; c0 += 64) {
-      const int t = c0 + lane;
-      const float wt = t < g1 ? fmaxf(0.f, __expf(zp[t] - lse[0]) - __expf(zq[t] - lse[1])) : 0.f;
-      float sc = wt;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float n = __shfl_up(sc, o, 64);
-        if (lane >= o) sc += n;
-      }
-      const unsigned long long hit = __ballot(wt > 0.f && run + sc > Tl);
-      if (hit) {
-        found = c0 + __builtin_ctzll(hit);
-        break;
-      }
-      const unsigned long long mass = __ballot(wt > 0.f);
-      if (mass) last = c0 + 63 - __builtin_clzll(mass);
-      run += __shfl(sc, 63, 64);
-    }
-    if (lane == 0) sh_res = found >= 0 ? found : last;
-  }
-  __syncthreads();
   if (tid == 0) {
-    int res = (Z > 0.f && sh_res >= 0) ? sh_res : amax;
     const bool ok = res >= 0 && res < V;   // false only for rows without a finite logit
     if (!ok) res = 0;
-    const int x = look[(long long)(m / d) * (d + 1) + (m % d) + 1];
-    draft_lp[m] = (x >= 0 && x < V) ? zq[x] - lse[1] : __int_as_float(0x7fc00000);
-    res_ids[m] = res;
-    res_lp[m] = ok ? zp[res] - lse[0] : __int_as_float(0x7fc00000);
+    const int x = look[(long long)(row / d) * (d + 1) + (row % d) + 1];
+    draft_lp[row] = (x >= 0 && x < V) ? zq[x] - lq : __int_as_float(0x7fc00000);
+    res_ids[row] = res;
+    res_lp[row] = ok ? zp[res] - lp : __int_as_float(0x7fc00000);
   }
 }
 
@@ -1200,10 +1309,19 @@ hipError_t rowstats_merge_launch(const RowStats& s, const LogitArgs& a, int M, h
 hipError_t logit_rows_launch(const LogitArgs& a, int M, hipStream_t st) {
   if (M == 0) return hipSuccess;
   if (a.kk > 16 || a.kk < 0) return hipErrorInvalidValue;
-  if (a.kk == 0) logit_rows_kernel<0><<<M, 256, 0, st>>>(a);
-  else if (a.kk <= 4) logit_rows_kernel<4><<<M, 256, 0, st>>>(a);
-  else if (a.kk <= 8) logit_rows_kernel<8><<<M, 256, 0, st>>>(a);
-  else logit_rows_kernel<16><<<M, 256, 0, st>>>(a);
+  // Long rows: 1024 threads where there are few (100 rows of 128256: 43
+  // against 64 us with 512), 512 where a CU has several (512 rows of 50257:
+  // 49 against 66 us).  Short rows: 256 threads (900 rows of 4001: 38 against
+  // 44 us).
+#define LOGIT_ROWS(NT)                                                   \
+  do {                                                                   \
+    if (a.want_lse) logit_rows_kernel<NT, true><<<M, NT, 0, st>>>(a);    \
+    else logit_rows_kernel<NT, false><<<M, NT, 0, st>>>(a);              \
+  } while (0)
+  if (a.V <= 8192) LOGIT_ROWS(256);
+  else if (M >= 384) LOGIT_ROWS(512);
+  else LOGIT_ROWS(1024);
+#undef LOGIT_ROWS
   return hipGetLastError();
 }
 
@@ -1224,7 +1342,9 @@ hipError_t select_launch(int B, int k, const float* scores, const float* reward,
 hipError_t soft_rows_launch(const float* zp, const float* zq, int M, int V, int d, const int* look, const float* v,
                             float* draft_lp, int* res_ids, float* res_lp, hipStream_t st) {
   if (M == 0) return hipSuccess;
-  soft_rows_kernel<<<M, 256, 0, st>>>(zp, zq, V, d, look, v, draft_lp, res_ids, res_lp);
+  // short rows: more of them per CU (800 rows of 4001: 15 against 35 us)
+  if (V <= 8192) soft_rows_kernel<256><<<M, 256, 0, st>>>(zp, zq, V, d, look, v, draft_lp, res_ids, res_lp);
+  else soft_rows_kernel<1024><<<M, 1024, 0, st>>>(zp, zq, V, d, look, v, draft_lp, res_ids, res_lp);
   return hipGetLastError();
 }
 
