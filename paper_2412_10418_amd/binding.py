@@ -196,13 +196,18 @@ def cdsl_op_gemm(A: torch.Tensor, B: torch.Tensor, C_out: Optional[torch.Tensor]
     return C_out
 
 
+def _row_outputs(M: int, kk: int, gather, dev):
+    """lp, amax, topk_ids, topk_lp: the library writes them whole (lp only
+    with a gather: zeros without one)."""
+    lp = (torch.zeros if gather is None else torch.empty)(M, dtype=torch.float32, device=dev)
+    return (lp, torch.empty(M, dtype=torch.int32, device=dev),
+            torch.empty((M, max(kk, 1)), dtype=torch.int32, device=dev),
+            torch.empty((M, max(kk, 1)), dtype=torch.float32, device=dev))
+
+
 def cdsl_op_logit_rows(logits: torch.Tensor, gather: Optional[torch.Tensor], kk: int):
     M, V = logits.shape
-    dev = logits.device
-    lp = torch.zeros(M, dtype=torch.float32, device=dev)
-    amax = torch.zeros(M, dtype=torch.int32, device=dev)
-    tk = torch.zeros((M, max(kk, 1)), dtype=torch.int32, device=dev)
-    tl = torch.zeros((M, max(kk, 1)), dtype=torch.float32, device=dev)
+    lp, amax, tk, tl = _row_outputs(M, kk, gather, logits.device)
     rc = lib().cdsl_op_logit_rows(_ptr(logits, torch.float32, "logits"), M, V,
                                   _ptr(gather, torch.int32, "gather"), kk, lp.data_ptr(),
                                   amax.data_ptr(), tk.data_ptr(), tl.data_ptr(), _stream())
@@ -220,11 +225,8 @@ def cdsl_op_lm_head_rows(A: torch.Tensor, B: torch.Tensor, gather: Optional[torc
     need = lib().cdsl_op_lm_head_rows_workspace(M, V, K, dt, kk)
     if need == 0:
         raise ValueError("shape not covered by the fused LM-head epilogue")
-    ws = torch.zeros(need, dtype=torch.uint8, device=dev)
-    lp = torch.zeros(M, dtype=torch.float32, device=dev)
-    amax = torch.zeros(M, dtype=torch.int32, device=dev)
-    tk = torch.zeros((M, max(kk, 1)), dtype=torch.int32, device=dev)
-    tl = torch.zeros((M, max(kk, 1)), dtype=torch.float32, device=dev)
+    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    lp, amax, tk, tl = _row_outputs(M, kk, gather, dev)
     rc = lib().cdsl_op_lm_head_rows(_ptr(A, torch.float32, "A"), _ptr(B, B.dtype, "B"), M, V, K, dt,
                                     _ptr(gather, torch.int32, "gather"), kk, lp.data_ptr(), amax.data_ptr(),
                                     tk.data_ptr(), tl.data_ptr(), ws.data_ptr(), need, _stream())
