@@ -524,7 +524,11 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
 }
 
 // Plain path for fp32 models: one wave per (row, head), 64 keys per chunk
-// (one per lane), online softmax, no MFMA.  Same cache layout and masks.
+// (one per lane), online softmax, no MFMA.  Same cache layout and masks.  A
+// chain of dependent steps, so a lane's dot product runs in four sums with its
+// key in 16-byte loads, and the values of a block of 16 keys are loaded
+// together (a dim's 16 slots are consecutive), with the probabilities
+// broadcast from the lanes by number.
 template <int HD>
 __global__ __launch_bounds__(64) void attn_f32(AttnArgs a) {
   const PassDesc& p = a.p;
@@ -565,8 +569,14 @@ __global__ __launch_bounds__(64) void attn_f32(AttnArgs a) {
       ok = key_valid(p, owner, base + t, ri, Lp);
       if (ok) {
         const float* kr = kbase + ((long long)blk * a.Hkv + kvh) * (kBlock * HD) + t * HD;
-        float dot = 0.f;
-        for (int d = 0; d < HD; ++d) dot = fmaf(q[d], kr[d], dot);
+        f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int d = 0; d < HD; d += 4) {
+          const f32x4 kv = *(const f32x4*)(kr + d), qv = *(const f32x4*)(q + d);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) d4[e] = fmaf(qv[e], kv[e], d4[e]);
+        }
+        const float dot = (d4[0] + d4[1]) + (d4[2] + d4[3]);
         s = dot * a.scale_log2;
       }
     }
@@ -579,16 +589,22 @@ __global__ __launch_bounds__(64) void attn_f32(AttnArgs a) {
     m_run = m_new;
 #pragma unroll
     for (int u = 0; u < PER; ++u) acc[u] *= corr;
-    for (int kk = 0; kk < 64; ++kk) {
-      const float pv = __shfl(pk, kk, 64);
-      const int bk = __shfl(blk, kk, 64), tk = __shfl(t, kk, 64);
-      if (pv != 0.f) {
-        const float* vr = vbase + ((long long)bk * a.Hkv + kvh) * (HD * kBlock) + tk;
+    const int nb = min(4, (nkeys - c0) / kBlock);   // nkeys is whole blocks
+    for (int bq = 0; bq < nb; ++bq) {
+      const int bk = __builtin_amdgcn_readlane(blk, bq * kBlock);
+      f32x4 vv[PER][kBlock / 4];
+      const float* vr = vbase + ((long long)bk * a.Hkv + kvh) * (HD * kBlock);
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-          int d = lane + 64 * u;
-          if (d < HD) acc[u] = fmaf(pv, vr[d * kBlock], acc[u]);
-        }
+      for (int u = 0; u < PER; ++u)
+#pragma unroll
+        for (int e = 0; e < kBlock / 4; ++e)
+          vv[u][e] = *(const f32x4*)(vr + min(lane + 64 * u, HD - 1) * kBlock + 4 * e);
+#pragma unroll
+      for (int kk = 0; kk < kBlock; ++kk) {
+        const float pv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pk), bq * kBlock + kk));
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+          acc[u] = pv != 0.f ? fmaf(pv, vv[u][kk / 4][kk % 4], acc[u]) : acc[u];   // slots without a key are skipped
       }
     }
   }

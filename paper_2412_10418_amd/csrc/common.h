@@ -11,6 +11,8 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2v;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+// four floats at any 4-byte alignment
+typedef f32x4 f32x4u __attribute__((aligned(4)));
 // native 16-byte vector for raw copies (HIP's uint4 wraps a union, which
 // keeps the optimizer from holding it in registers)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

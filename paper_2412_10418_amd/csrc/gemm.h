@@ -38,7 +38,8 @@ struct GemmOperand {
 };
 
 // Where the product goes: fp32 [M, ldc] for kEpiStore / kEpiResidual, the
-// bf16 hi / lo planes [M, ldc] of silu(gate) * up for kEpiSwiGLU.
+// bf16 hi / lo planes (fp32 models: fp32) [M, ldc] of silu(gate) * up for
+// kEpiSwiGLU.
 struct GemmOut {
   float* f32;
   bf16* hi;
@@ -50,9 +51,9 @@ struct GemmOut {
 // planes, two MFMA products per step); dtype 0: W fp32 (A fp32).
 //   kEpiStore:    C  = product
 //   kEpiResidual: C += product
-//   kEpiSwiGLU:   (bf16 only) W packs, per group of 32 rows, 16 gate rows
+//   kEpiSwiGLU:   W packs, per group of 32 rows, 16 gate rows
 //                 then the 16 matching up rows; the output (ldc = N/2)
-//                 receives silu(gate) * up as hi / lo planes.
+//                 receives silu(gate) * up as hi / lo planes (fp32).
 //   kEpiRowStats: no C; the product's row statistics per column tile go to
 //                 *rs (RowStats in common.h), whose tiles field the launch
 //                 sets.  The K dimension is never split for it.
@@ -85,7 +86,6 @@ hipError_t gemm_launch(const GemmOperand& A, const void* B, const GemmOut& out, 
                        int epi, void* ws, size_t ws_bytes, hipStream_t st, bool prefill = false,
                        GemmHook* hook = nullptr, int* deferred = nullptr, RowStats* rs = nullptr,
                        const RopeEpi* rope = nullptr, size_t max_ws = SIZE_MAX);
-hipError_t swiglu_f32_launch(const float* gu, float* act, int M, int F, hipStream_t st);
 hipError_t split_planes_launch(const float* x, bf16* hi, bf16* lo, long long n, hipStream_t st);
 
 }  // namespace cdsl

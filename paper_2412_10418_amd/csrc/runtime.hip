@@ -67,7 +67,6 @@ struct Workspace {
   // projection inputs: hi / lo bf16 planes (bf16 weights) or fp32
   bf16 *uh = nullptr, *ul = nullptr, *oh = nullptr, *ol = nullptr, *ah = nullptr, *al = nullptr;
   float *u32 = nullptr, *o32 = nullptr, *act32 = nullptr;
-  float* gu32 = nullptr;
   float* logits = nullptr;
   // LM-head row statistics per column tile (the fused epilogue); rs_cap rows
   // x tiles, times the top-k width for the candidate lists
@@ -432,7 +431,6 @@ void alloc_workspace(cdsl_ctx* c) {
     w.u32 = dev_alloc<float>(c, M * Dm);
     w.o32 = dev_alloc<float>(c, M * HQm);
     w.act32 = dev_alloc<float>(c, M * Fm);
-    w.gu32 = dev_alloc<float>(c, M * 2 * Fm);
   }
   w.logits = dev_alloc<float>(c, (size_t)w.Mlog * Vm);
   for (auto& md : c->m)
@@ -576,7 +574,7 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
   const bool bf = dt == CDSL_BF16;
   const GemmOperand Au{w.uh, w.ul, w.u32}, Ao{w.oh, w.ol, w.o32}, Aact{w.ah, w.al, w.act32};
   const GemmOut to_qkv{w.qkv, nullptr, nullptr, md.qkv_n}, to_h{w.h, nullptr, nullptr, D};
-  const GemmOut to_act{nullptr, w.ah, w.al, F}, to_gu{w.gu32, nullptr, nullptr, 2 * F};
+  const GemmOut to_act{w.act32, w.ah, w.al, F};
   // Residual projections (W_o, W_down) and the q/k/v projection may leave
   // their K split unreduced: the planes are folded by the kernel that
   // consumes the result (RMSNorm of the residual stream, rotary + KV
@@ -621,13 +619,7 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
       CK(rmsnorm_launch(w.h, md.g2[l], w.u32, w.uh, w.ul, M, D, k.rms_eps, 0, 1, nullptr, c->st,
                         so > 1 ? planes_ws : nullptr, so > 1 ? so : 0));
     }
-    if (bf) {
-      gemm(c, Au, md.wgu[l], to_act, M, 2 * F, D, kEpiSwiGLU, prefill);
-    } else {
-      gemm(c, Au, md.wgu[l], to_gu, M, 2 * F, D, kEpiStore, prefill);
-      Span sp(c, CDSL_K_ROWWISE, 0.0, (double)M * F * 12.0);
-      CK(swiglu_f32_launch(w.gu32, w.act32, M, F, c->st));
-    }
+    gemm(c, Au, md.wgu[l], to_act, M, 2 * F, D, kEpiSwiGLU, prefill);
     const int sd = gemm(c, Aact, md.wd[l], to_h, M, D, F, kEpiResidual, prefill, bf);
     const bool last = l + 1 == k.n_layers;
     if (!last || sd > 1) {

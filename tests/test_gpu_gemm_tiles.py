@@ -96,3 +96,22 @@ def test_static_scratch_takes_a_smaller_split_than_the_plan():
 
 
 STATIC_SHAPE = (716, 2830, 12000)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 33, 16), (15, 384, 48), (17, 65, 80), (16, 2048, 256), (33, 1000, 128), (130, 777, 640),
+                                   (512, 2047, 1024), (500, 1030, 336)])
+def test_fp32_projection_at_tile_edges(M, N, K):
+    """fp32 weights: fp32 sums (K terms: below 2^-24 sqrt(K) of the row times
+    column norms, far inside 2e-6 of the largest output), operands at any
+    4-byte alignment, and every row the same bits whatever the batch."""
+    from paper_2412_10418_amd.binding import cdsl_op_gemm
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    flat = torch.randn(M * K + N * K + 8, generator=g, device="cuda")
+    a, w = flat[1:1 + M * K].view(M, K), flat[3 + M * K:3 + M * K + N * K].view(N, K)
+    buf = torch.full((M * N + 4096,), 7.0, device="cuda")
+    got = cdsl_op_gemm(a, w, buf[:M * N].view(M, N))
+    ref = torch.matmul(a.double(), w.double().t())
+    assert float((got.double() - ref).abs().max() / ref.abs().max()) < 2e-6
+    assert bool((buf[M * N:] == 7.0).all())
+    for r in (0, M // 2, M - 1):
+        assert torch.equal(cdsl_op_gemm(a[r:r + 1].clone(), w), got[r:r + 1])
