@@ -28,6 +28,7 @@ constexpr int kAttnMaxSplits = 16;
 struct AttnPlan {
   int row_tiles, row_groups, threads;
   int kw;                 // key groups per row tile (1, 2 or 4)
+  int rpw;                // row tiles per wave (1 or 2)
   int nsplit, blocks_per_split;
 };
 

@@ -126,10 +126,16 @@ __device__ __forceinline__ bool window_sees(const Window& w, int owner, int base
 // table, then one per iteration) is then short.  Eight waves put up to
 // four row tiles of a (prompt, KV head) in one workgroup, so its keys are
 // read from memory once for all of them.
-template <int HD, int KW, int NW>
+//
+// RPW = row tiles per wave.  The verification of many rows and the prefill
+// are bound by the LDS reads of K and V (32 KB per wave and pair at hd = 128,
+// 2048 cycles for eight waves against 1536 of MFMAs); two row tiles per wave
+// use every fragment twice.
+template <int HD, int KW, int NW, int RPW = 1>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void attn_split(AttnArgs a) {
   constexpr int NT = 64 * NW;
-  constexpr int RTW = NW / KW;                 // row tiles per workgroup
+  constexpr int RTW = NW / KW * RPW;           // row tiles per workgroup
+  static_assert(KW == 1 || RPW == 1, "key groups merge one row tile per wave");
   constexpr int NPI = KW;                      // pairs per iteration
   constexpr int KCH = HD / 8;                  // 16-byte chunks per K row
   constexpr int KPL = 2 * kBlock * HD;         // LDS K plane: 2 blocks x 16 keys x HD
@@ -195,23 +201,27 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
   // this wave's rows (a wave past the last row still stages key blocks)
   const int rt = wave / KW, kw = wave % KW;
-  const int rw0 = wg_r0 + rt * 16;
+  const int rw0 = wg_r0 + rt * 16 * RPW;
   const bool wave_has_rows = rw0 < nrows;
-  const RowInfo ri = decode_row(p, rw0 + lr, nrows, bi, kvh, G, Lp);
-  const Window wwin = row_window(p, min(rw0, nrows - 1), min(rw0 + 15, nrows - 1), G, Lp);
+  RowInfo ri[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) ri[r] = decode_row(p, rw0 + 16 * r + lr, nrows, bi, kvh, G, Lp);
+  const Window wwin = row_window(p, min(rw0, nrows - 1), min(rw0 + 16 * RPW - 1, nrows - 1), G, Lp);
 
   // Q^T fragments (B operand): row lr, dims 32s + 8lg .. +8, as hi / lo;
   // issued before the key-block list so the two latencies overlap
-  float4 qx[KS][2];
+  float4 qx[RPW][KS][2];
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    qx[s][0] = qx[s][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (ri.valid) {
-      const float* qrow = a.Q + ((long long)ri.m * a.H + ri.h) * HD + s * 32 + lg * 8;
-      qx[s][0] = *(const float4*)qrow;
-      qx[s][1] = *(const float4*)(qrow + 4);
+  for (int r = 0; r < RPW; ++r)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      qx[r][s][0] = qx[r][s][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (ri[r].valid) {
+        const float* qrow = a.Q + ((long long)ri[r].m * a.H + ri[r].h) * HD + s * 32 + lg * 8;
+        qx[r][s][0] = *(const float4*)qrow;
+        qx[r][s][1] = *(const float4*)(qrow + 4);
+      }
     }
-  }
 
   // list of the key blocks that some row of the workgroup can see
   if (wave == 0) {
@@ -240,9 +250,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int npairs = (n + 1) / 2;
   const int niters = (npairs + NPI - 1) / NPI;
 
-  bf16x8 qh[KS], ql[KS];
+  bf16x8 qh[RPW][KS], ql[RPW][KS];
 #pragma unroll
-  for (int s = 0; s < KS; ++s) split8(qx[s][0], qx[s][1], qh[s], ql[s]);
+  for (int r = 0; r < RPW; ++r)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) split8(qx[r][s][0], qx[r][s][1], qh[r][s], ql[r][s]);
 
   // staging: chunk q = tid + NT * u of a pair is region q / UCH (K of block
   // A, K of block B, V of A, V of B) at 16-byte offset q % UCH of the unit.
@@ -299,23 +311,31 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
   };
 
-  f32x4 acc[DT];
+  f32x4 acc[RPW][DT];
 #pragma unroll
-  for (int t = 0; t < DT; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  // Running max m_run (log2 units) and sum l_run of this lane's row.  The
+  for (int r = 0; r < RPW; ++r)
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[r][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // Running max m_run (log2 units) and sum l_run of this lane's rows.  The
   // exponentials use a possibly stale max: it is only raised (and O, l
   // rescaled) once the true max exceeds it by more than kLazy, so
   // probabilities stay below 2^kLazy and the rescale is rare.  O / l does
   // not depend on which max was used.
   constexpr float kLazy = 8.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run[RPW], l_run[RPW];
   // Visibility of a key at absolute slot x of a block of owner o to this
   // lane's row: x <= lim_pre for prefix blocks (o < 0), x <= lim_own for
   // the suffix blocks of the row's own beam, never for other beams.
-  const int lim_pre = !ri.valid ? -1 : (p.mode == kSuffix ? Lp - 1 : ri.pos);
-  const int lim_own = ri.valid ? p.j0 + ri.j : -1;
-  auto limit = [&](int owner, int base) __attribute__((always_inline)) {
-    return (owner < 0 ? lim_pre : (owner == ri.i ? lim_own : -1)) - base;
+  int lim_pre[RPW], lim_own[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    m_run[r] = -INFINITY;
+    l_run[r] = 0.f;
+    lim_pre[r] = !ri[r].valid ? -1 : (p.mode == kSuffix ? Lp - 1 : ri[r].pos);
+    lim_own[r] = ri[r].valid ? p.j0 + ri[r].j : -1;
+  }
+  auto limit = [&](int r, int owner, int base) __attribute__((always_inline)) {
+    return (owner < 0 ? lim_pre[r] : (owner == ri[r].i ? lim_own[r] : -1)) - base;
   };
 
   // One pair of key blocks (A, B) from LDS buffer buf.  Scores transposed:
@@ -334,7 +354,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const bool relB = hasB && window_sees(wwin, ownB, baseB);
     if (!wave_has_rows || (!relA && !relB)) return;
     const bf16* L = lds[buf][slot];
-    f32x4 sA = {0.f, 0.f, 0.f, 0.f}, sB = sA;
+    f32x4 sA[RPW], sB[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) sA[r] = sB[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int rowA = lr, rowB = kBlock + lr;
@@ -342,57 +364,64 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       const int offB = rowB * HD + (((4 * s + lg) ^ (rowB & 7)) << 3);
       const bf16x8 kah = *(const bf16x8*)(L + offA), kal = *(const bf16x8*)(L + KPL + offA);
       const bf16x8 kbh = *(const bf16x8*)(L + offB), kbl = *(const bf16x8*)(L + KPL + offB);
-      sA = mfma3(kah, kal, qh[s], ql[s], sA);
-      sB = mfma3(kbh, kbl, qh[s], ql[s], sB);
-    }
-    const int tA = limit(ownA, baseA) - 4 * lg;
-    const int tB = (hasB ? limit(ownB, baseB) : -1) - 4 * lg;
-    float sv[8];
-    float mt = -INFINITY;
-    if (__all(tA >= 3 && tB >= 3)) {   // every key of both blocks visible
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sv[e] = sA[e] * a.scale_log2;
-        sv[4 + e] = sB[e] * a.scale_log2;
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sv[e] = e <= tA ? sA[e] * a.scale_log2 : -INFINITY;
-        sv[4 + e] = e <= tB ? sB[e] * a.scale_log2 : -INFINITY;
+      for (int r = 0; r < RPW; ++r) {
+        sA[r] = mfma3(kah, kal, qh[r][s], ql[r][s], sA[r]);
+        sB[r] = mfma3(kbh, kbl, qh[r][s], ql[r][s], sB[r]);
       }
     }
+    bf16x8 ph[RPW], pl[RPW];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) mt = fmaxf(mt, sv[e]);
-    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const bool raise = mt > m_run + kLazy;   // true for the first visible key
-    if (__ballot(raise)) {
-      const float m_to = raise ? mt : m_run;
-      const float corr = m_to == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_to);
-      l_run *= corr;
+    for (int r = 0; r < RPW; ++r) {
+      const int tA = limit(r, ownA, baseA) - 4 * lg;
+      const int tB = (hasB ? limit(r, ownB, baseB) : -1) - 4 * lg;
+      float sv[8];
+      float mt = -INFINITY;
+      if (__all(tA >= 3 && tB >= 3)) {   // every key of both blocks visible
 #pragma unroll
-      for (int t = 0; t < DT; ++t) acc[t] *= corr;
-      m_run = m_to;
+        for (int e = 0; e < 4; ++e) {
+          sv[e] = sA[r][e] * a.scale_log2;
+          sv[4 + e] = sB[r][e] * a.scale_log2;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sv[e] = e <= tA ? sA[r][e] * a.scale_log2 : -INFINITY;
+          sv[4 + e] = e <= tB ? sB[r][e] * a.scale_log2 : -INFINITY;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mt = fmaxf(mt, sv[e]);
+      mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+      mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+      const bool raise = mt > m_run[r] + kLazy;   // true for the first visible key
+      if (__ballot(raise)) {
+        const float m_to = raise ? mt : m_run[r];
+        const float corr = m_to == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run[r] - m_to);
+        l_run[r] *= corr;
+#pragma unroll
+        for (int t = 0; t < DT; ++t) acc[r][t] *= corr;
+        m_run[r] = m_to;
+      }
+      const float m_use = m_run[r] == -INFINITY ? 0.f : m_run[r];
+      float psum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float pv = __builtin_amdgcn_exp2f(sv[e] - m_use);
+        psum += pv;
+        const bf16 h = (bf16)pv;
+        ph[r][e] = h;
+        pl[r][e] = (bf16)(pv - (float)h);
+      }
+      l_run[r] += psum;
     }
-    const float m_use = m_run == -INFINITY ? 0.f : m_run;
-    float psum = 0.f;
-    bf16x8 ph, pl;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float pv = __builtin_amdgcn_exp2f(sv[e] - m_use);
-      psum += pv;
-      const bf16 h = (bf16)pv;
-      ph[e] = h;
-      pl[e] = (bf16)(pv - (float)h);
-    }
-    l_run += psum;
     // V^T fragment: dim 16t + lr, keys 4lg..4lg+3 of A then of B
 #pragma unroll
     for (int t = 0; t < DT; ++t) {
       const int voff = 2 * KPL + (t * 16 + lr) * 32 + lg * 8;
       const bf16x8 vh = *(const bf16x8*)(L + voff), vl = *(const bf16x8*)(L + VPL + voff);
-      acc[t] = mfma3(vh, vl, ph, pl, acc[t]);
+#pragma unroll
+      for (int r = 0; r < RPW; ++r) acc[r][t] = mfma3(vh, vl, ph[r], pl[r], acc[r][t]);
     }
   };
 
@@ -410,8 +439,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     __syncthreads();
   }
 
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    l_run[r] += __shfl_xor(l_run[r], 16, 64);
+    l_run[r] += __shfl_xor(l_run[r], 32, 64);
+  }
   if constexpr (KW > 1) {
     // key groups 1.. hand (m, l, O) to group 0 of their row tile through
     // LDS (free after the loop's last barrier); group 0 merges them in
@@ -420,12 +452,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     float* X = (float*)&lds[0][0][0];
     if (wave_has_rows && kw > 0) {
       float* x = X + (rt * (KW - 1) + kw - 1) * SLOT;
-      x[lane] = m_run;
-      x[64 + lane] = l_run;
+      x[lane] = m_run[0];
+      x[64 + lane] = l_run[0];
 #pragma unroll
       for (int t = 0; t < DT; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[(2 + 4 * t + e) * 64 + lane] = acc[t][e];
+        for (int e = 0; e < 4; ++e) x[(2 + 4 * t + e) * 64 + lane] = acc[0][t][e];
     }
     __syncthreads();
     if (kw > 0 || !wave_has_rows) return;
@@ -433,44 +465,48 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int q = 1; q < KW; ++q) {
       const float* x = X + (rt * (KW - 1) + q - 1) * SLOT;
       const float mq = x[lane], lq = x[64 + lane];
-      const float mn = fmaxf(m_run, mq);
-      const float s0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
+      const float mn = fmaxf(m_run[0], mq);
+      const float s0 = m_run[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[0] - mn);
       const float s1 = mq == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mq - mn);
-      l_run = l_run * s0 + lq * s1;
+      l_run[0] = l_run[0] * s0 + lq * s1;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[t][e] = acc[t][e] * s0 + x[(2 + 4 * t + e) * 64 + lane] * s1;
-      m_run = mn;
+        for (int e = 0; e < 4; ++e) acc[0][t][e] = acc[0][t][e] * s0 + x[(2 + 4 * t + e) * 64 + lane] * s1;
+      m_run[0] = mn;
     }
   }
-  if (!wave_has_rows || !ri.valid) return;
-  const long long rowid = (long long)ri.m * a.H + ri.h;
-  // lane (row lr, lg) holds dims 16t + 4lg .. +3
-  if (a.nsplit == 1) {
-    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+  if (!wave_has_rows) return;
 #pragma unroll
-    for (int t = 0; t < DT; ++t) {
-      bf16x4 hv, lv;
+  for (int r = 0; r < RPW; ++r) {
+    if (!ri[r].valid) continue;
+    const long long rowid = (long long)ri[r].m * a.H + ri[r].h;
+    // lane (row lr, lg) holds dims 16t + 4lg .. +3
+    if (a.nsplit == 1) {
+      const float inv = l_run[r] > 0.f ? 1.f / l_run[r] : 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        bf16 h, l;
-        split_bf16(acc[t][e] * inv, h, l);
-        hv[e] = h;
-        lv[e] = l;
+      for (int t = 0; t < DT; ++t) {
+        bf16x4 hv, lv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          bf16 h, l;
+          split_bf16(acc[r][t][e] * inv, h, l);
+          hv[e] = h;
+          lv[e] = l;
+        }
+        const long long o = rowid * HD + t * 16 + lg * 4;
+        *(bf16x4*)(a.Ohi + o) = hv;
+        *(bf16x4*)(a.Olo + o) = lv;
       }
-      const long long o = rowid * HD + t * 16 + lg * 4;
-      *(bf16x4*)(a.Ohi + o) = hv;
-      *(bf16x4*)(a.Olo + o) = lv;
-    }
-  } else {
-    const long long prow = (long long)split * a.rows_total + rowid;
-    float* po = a.part_o + prow * HD + lg * 4;
+    } else {
+      const long long prow = (long long)split * a.rows_total + rowid;
+      float* po = a.part_o + prow * HD + lg * 4;
 #pragma unroll
-    for (int t = 0; t < DT; ++t) *(f32x4*)(po + t * 16) = acc[t];
-    if (lg == 0) {
-      a.part_ml[prow * 2] = m_run;
-      a.part_ml[prow * 2 + 1] = l_run;
+      for (int t = 0; t < DT; ++t) *(f32x4*)(po + t * 16) = acc[r][t];
+      if (lg == 0) {
+        a.part_ml[prow * 2] = m_run[r];
+        a.part_ml[prow * 2 + 1] = l_run[r];
+      }
     }
   }
 }
@@ -638,8 +674,9 @@ AttnPlan attn_plan(const PassDesc& p, int H, int Hkv, int hd, int dtype, int max
   // group).
   pl.row_tiles = (nrows + 15) / 16;
   pl.threads = 256;
+  pl.rpw = 1;
   pl.kw = pl.row_tiles <= 2 ? (hd == 64 ? 4 : 2) : 1;
-  if (hd == 64 && pl.row_tiles >= 2 && pl.row_tiles <= 4 && p.nb * Hkv >= 256) {
+  if (hd == 64 && pl.row_tiles >= 2 && pl.row_tiles <= 4 && (p.nb * Hkv >= 256 || ((nK + 1) / 2 + 3) / 4 > 8)) {
     // eight waves: 2 row tiles x 4 key groups, or 4 x 2; the keys are read
     // once per (prompt, KV head) instead of once per row tile.  With fewer
     // than 256 (prompt, KV head) pairs the pass is latency-bound and twice
@@ -648,12 +685,12 @@ AttnPlan attn_plan(const PassDesc& p, int H, int Hkv, int hd, int dtype, int max
     pl.threads = 512;
     pl.kw = pl.row_tiles == 2 ? 4 : 2;
   } else if (pl.row_tiles > 4) {
-    // eight row tiles per workgroup: each key block is read once per 128
-    // rows (the verification of long prefixes) instead of once per 64
-    pl.threads = 512;
-    pl.kw = 1;
+    // eight row tiles per workgroup, two per wave: each key block is read once
+    // per 128 rows (the verification of long prefixes) instead of once per
+    // 64, and each fragment from LDS once per 32 rows
+    pl.rpw = 2;
   }
-  const int rtw = pl.threads / 64 / pl.kw;
+  const int rtw = pl.threads / 64 / pl.kw * pl.rpw;
   pl.row_groups = (pl.row_tiles + rtw - 1) / rtw;
   // enough workgroups for two per CU, >= 1 key-block pair per split, and at
   // most kAttnMaxList key blocks per split; no split (and no combine
@@ -695,15 +732,16 @@ hipError_t attn_launch(const AttnArgs& args, const AttnPlan& pl, int hd, int dty
   if (hd == 64) {
     if (pl.threads == 512) {
       if (pl.kw == 4) attn_split<64, 4, 8><<<grid, 512, 0, st>>>(a);
-      else if (pl.kw == 2) attn_split<64, 2, 8><<<grid, 512, 0, st>>>(a);
-      else attn_split<64, 1, 8><<<grid, 512, 0, st>>>(a);
+      else attn_split<64, 2, 8><<<grid, 512, 0, st>>>(a);
+    } else if (pl.rpw == 2) {
+      attn_split<64, 1, 4, 2><<<grid, 256, 0, st>>>(a);
     } else if (pl.kw == 4) {
       attn_split<64, 4, 4><<<grid, 256, 0, st>>>(a);
     } else {
       attn_split<64, 1, 4><<<grid, 256, 0, st>>>(a);
     }
   } else if (hd == 128) {
-    if (pl.threads == 512) attn_split<128, 1, 8><<<grid, 512, 0, st>>>(a);
+    if (pl.rpw == 2) attn_split<128, 1, 4, 2><<<grid, 256, 0, st>>>(a);
     else if (pl.kw == 2) attn_split<128, 2, 4><<<grid, 256, 0, st>>>(a);
     else attn_split<128, 1, 4><<<grid, 256, 0, st>>>(a);
   } else {
