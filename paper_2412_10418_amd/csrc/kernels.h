@@ -82,6 +82,9 @@ hipError_t promote_launch(int B, int k, const KVPool& pool, int n_layers, const 
                           int s_stride_b, int s_stride_i, int dtype, hipStream_t st);
 hipError_t advance_launch(int B, const int* stage, int stage_stride, int dlim, int* Lp, hipStream_t st);
 hipError_t add_launch(int n, const int* ids, int* v, int delta, hipStream_t st);
+// q2[r] / h2[r] = row r * R + R - 1 of q [.][Q] / h [.][D]
+hipError_t last_rows_launch(int rows, int R, const float* q, int Q, const float* h, int D, float* q2, float* h2,
+                            hipStream_t st);
 hipError_t fill_int_launch(int* p, int v, long long n, hipStream_t st);
 hipError_t heads_to_lookaheads_launch(int BK, int d, const int* beams, int* look, hipStream_t st);
 

@@ -1145,6 +1145,15 @@ __global__ void add_kernel(int n, const int* __restrict__ ids, int* __restrict__
   if (u < n) v[ids ? ids[u] : u] += delta;
 }
 
+// Row r of q2 / h2 = row r * R + R - 1 of q / h (the last row of each prompt).
+__global__ __launch_bounds__(256) void last_rows_kernel(const float* __restrict__ q, const float* __restrict__ h, int R,
+                                                        int Q, int D, float* __restrict__ q2, float* __restrict__ h2) {
+  const int r = blockIdx.x;
+  const long long src = (long long)r * R + R - 1;
+  for (int c = threadIdx.x * 4; c < Q; c += 1024) *(float4*)(q2 + (long long)r * Q + c) = *(const float4*)(q + src * Q + c);
+  for (int c = threadIdx.x * 4; c < D; c += 1024) *(float4*)(h2 + (long long)r * D + c) = *(const float4*)(h + src * D + c);
+}
+
 __global__ void fill_int_kernel(int* __restrict__ p, int v, long long n) {
   long long u = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (u < n) p[u] = v;
@@ -1171,13 +1180,18 @@ hipError_t rmsnorm_launch(float* x, const float* g, float* out32, bf16* ohi, bf1
                           float eps, int last_only, int R, float* hid, hipStream_t st, const float* part, int S) {
   if (rows == 0) return hipSuccess;
   if (S > 0 && last_only) return hipErrorInvalidValue;
-  if (D % 4 != 0 || D > 4 * 256 * kNormU) return hipErrorInvalidValue;
-  // few rows (the rollout): more threads per row keep more split planes'
-  // loads in flight
-  if (rows < 256)
-    rmsnorm_rows<1024><<<rows, 1024, 0, st>>>(x, g, out32, ohi, olo, D, eps, last_only, R, hid, part, S, rows);
-  else
-    rmsnorm_rows<256><<<rows, 256, 0, st>>>(x, g, out32, ohi, olo, D, eps, last_only, R, hid, part, S, rows);
+  if (D % 4 != 0 || D > 4 * 256 * kNormU) return hipErrorInvalidValue;   // (narrower launches hold fewer columns)
+  // Few rows (the rollout): a thread per 16 bytes of the row, so that all of
+  // its loads (and those of the split planes) are in flight at once and no
+  // wave is launched for nothing.
+#define NORM(NT)                                                                                             \
+  rmsnorm_rows<NT><<<rows, NT, 0, st>>>(x, g, out32, ohi, olo, D, eps, last_only, R, hid, part, S, rows)
+  if (rows >= 256) NORM(256);
+  else if (D <= 256) NORM(64);
+  else if (D <= 1024) NORM(256);
+  else if (D <= 2048) NORM(512);
+  else NORM(1024);
+#undef NORM
   return hipGetLastError();
 }
 
@@ -1441,6 +1455,14 @@ hipError_t advance_launch(int B, const int* stage, int stage_stride, int dlim, i
 hipError_t add_launch(int n, const int* ids, int* v, int delta, hipStream_t st) {
   if (n == 0) return hipSuccess;
   add_kernel<<<(n + 127) / 128, 128, 0, st>>>(n, ids, v, delta);
+  return hipGetLastError();
+}
+
+hipError_t last_rows_launch(int rows, int R, const float* q, int Q, const float* h, int D, float* q2, float* h2,
+                            hipStream_t st) {
+  if (rows == 0) return hipSuccess;
+  if (Q % 4 != 0 || D % 4 != 0) return hipErrorInvalidValue;
+  last_rows_kernel<<<rows, 256, 0, st>>>(q, h, R, Q, D, q2, h2);
   return hipGetLastError();
 }
 

@@ -521,13 +521,15 @@ void logit_rows(cdsl_ctx* c, const LogitArgs& la, int M);
 // (argmax, gathered log-prob, top-k): the LM head then leaves per-tile row
 // statistics and a merge kernel writes those outputs, so no logits reach
 // memory.  Without fuse (speculative sampling, which reads whole rows) the
-// head writes the logits.
+// head writes the logits.  last_Lp ([B] device: the prefix length plus R - 1):
+// with last_only, the last layer goes on with the last rows alone.
 void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, long long sum_prefix_len,
               bool want_logits, bool last_only, float* hid, bool prefill = false, float* logits_out = nullptr,
-              int logits_ld = 0, const LogitArgs* fuse = nullptr) {
+              int logits_ld = 0, const LogitArgs* fuse = nullptr, const int* last_Lp = nullptr) {
   Workspace& w = c->ws;
   const auto& k = md.c;
-  const int M = p.M();
+  int M = p.M();
+  float* h = w.h;
   const int D = k.d_model, F = k.ffn_dim, H = k.n_heads, Hkv = k.n_kv_heads, hd = md.hd;
   const int dt = k.dtype;
   if (M > w.Mmax) {
@@ -545,11 +547,11 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
   const double R = p.R, kp = p.kp;
   const double pre_tok = p.mode == kSuffix ? (double)sum_prefix_len : (double)sum_prefix_len + p.nb * R;
   const double suf_tok = p.mode == kSuffix ? (double)p.nb * kp * (p.j0 + R) : 0.0;
-  const double attn_bytes = (pre_tok + suf_tok) * kvtok + 2.0 * M * (double)H * hd * es;
+  double attn_bytes = (pre_tok + suf_tok) * kvtok + 2.0 * M * (double)H * hd * es;
   const double vis = p.mode == kSuffix
                          ? kp * (R * ((double)sum_prefix_len + p.nb * (double)p.j0) + p.nb * R * (R + 1) / 2)
                          : R * (double)sum_prefix_len + p.nb * R * (R + 1) / 2;
-  const double attn_flops = 4.0 * hd * (double)H * vis;
+  double attn_flops = 4.0 * hd * (double)H * vis;
   AttnPlan pl = attn_plan(p, H, Hkv, hd, dt, max_prefix_len, kMaxSplits);
   if (pl.nsplit > 1 && (size_t)M * H > w.part_rows) {
     pl = attn_plan(p, H, Hkv, hd, dt, max_prefix_len, 1);
@@ -568,12 +570,13 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
   aa.scale_log2 = (float)(1.4426950408889634 / sqrt((double)hd));
   aa.part_o = w.part_o;
   aa.part_ml = w.part_ml;
-  const double norm_bytes = (double)M * D * (4.0 + es);
+  double norm_bytes = (double)M * D * (4.0 + es);
   const double rope_bytes = (double)M * md.qkv_n * (4.0 + es);
   const double comb_bytes = (double)pl.nsplit * M * H * (hd + 2) * 4.0 + (double)M * H * hd * es;
   const bool bf = dt == CDSL_BF16;
   const GemmOperand Au{w.uh, w.ul, w.u32}, Ao{w.oh, w.ol, w.o32}, Aact{w.ah, w.al, w.act32};
-  const GemmOut to_qkv{w.qkv, nullptr, nullptr, md.qkv_n}, to_h{w.h, nullptr, nullptr, D};
+  const GemmOut to_qkv{w.qkv, nullptr, nullptr, md.qkv_n};
+  GemmOut to_h{h, nullptr, nullptr, D};
   const GemmOut to_act{w.act32, w.ah, w.al, F};
   // Residual projections (W_o, W_down) and the q/k/v projection may leave
   // their K split unreduced: the planes are folded by the kernel that
@@ -605,6 +608,26 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
                         sq > 1 ? sq : 0));
     }
     aa.layer = l;
+    const bool last = l + 1 == k.n_layers;
+    // the last layer's K and V are written; nothing after them is read when
+    // no logits are wanted, and only the last rows when only theirs are
+    if (last && !want_logits) return;
+    if (last && last_only && p.R > 1 && last_Lp) {
+      const int rows = p.nb * p.kp;
+      CK(last_rows_launch(rows, p.R, w.q, H * hd, w.h, D, w.qkv, w.qkv + (size_t)rows * H * hd, c->st));
+      aa.p.R = 1;
+      aa.p.Lp = last_Lp;
+      aa.Q = w.qkv;
+      aa.rows_total = (long long)rows * H;
+      h = w.qkv + (size_t)rows * H * hd;
+      to_h.f32 = h;
+      M = rows;
+      norm_bytes = (double)M * D * (4.0 + es);
+      attn_flops = 4.0 * hd * (double)H * pre_tok;
+      attn_bytes = pre_tok * kvtok + 2.0 * M * (double)H * hd * es;
+      pl = attn_plan(aa.p, H, Hkv, hd, dt, max_prefix_len + p.R - 1, kMaxSplits);
+      if (pl.nsplit > 1 && (size_t)M * H > w.part_rows) pl = attn_plan(aa.p, H, Hkv, hd, dt, max_prefix_len + p.R - 1, 1);
+    }
     {
       Span sp(c, CDSL_K_ATTENTION, attn_flops, attn_bytes);
       CK(attn_launch(aa, pl, hd, dt, c->st));
@@ -616,25 +639,26 @@ void run_pass(cdsl_ctx* c, Model& md, const PassDesc& p, int max_prefix_len, lon
     const int so = gemm(c, Ao, md.wo[l], to_h, M, D, H * hd, kEpiResidual, prefill, bf);
     {
       Span sp(c, CDSL_K_ROWWISE, 0.0, norm_bytes + (so > 1 ? (double)(so + 1) * M * D * 4.0 : 0.0));
-      CK(rmsnorm_launch(w.h, md.g2[l], w.u32, w.uh, w.ul, M, D, k.rms_eps, 0, 1, nullptr, c->st,
+      CK(rmsnorm_launch(h, md.g2[l], w.u32, w.uh, w.ul, M, D, k.rms_eps, 0, 1, nullptr, c->st,
                         so > 1 ? planes_ws : nullptr, so > 1 ? so : 0));
     }
     gemm(c, Au, md.wgu[l], to_act, M, 2 * F, D, kEpiSwiGLU, prefill);
     const int sd = gemm(c, Aact, md.wd[l], to_h, M, D, F, kEpiResidual, prefill, bf);
-    const bool last = l + 1 == k.n_layers;
     if (!last || sd > 1) {
       // next layer's attention norm (or, after the last layer, only the
       // fold: the final norm below may take just the last rows)
       Span sp(c, CDSL_K_ROWWISE, 0.0, (last ? 0.0 : norm_bytes) + (sd > 1 ? (double)(sd + 1) * M * D * 4.0 : 0.0));
-      CK(rmsnorm_launch(w.h, last ? nullptr : md.g1[l + 1], w.u32, w.uh, w.ul, M, D, k.rms_eps, 0, 1, nullptr, c->st,
+      CK(rmsnorm_launch(h, last ? nullptr : md.g1[l + 1], w.u32, w.uh, w.ul, M, D, k.rms_eps, 0, 1, nullptr, c->st,
                         sd > 1 ? planes_ws : nullptr, sd > 1 ? sd : 0));
     }
   }
   if (!want_logits) return;
+  const bool compact = M < p.M();   // the rows are the last ones already
   const int rows = last_only ? p.nb * p.kp : M;
   {
     Span sp(c, CDSL_K_ROWWISE, 0.0, (double)rows * D * (4.0 + es));
-    CK(rmsnorm_launch(w.h, md.gf, w.u32, w.uh, w.ul, rows, D, k.rms_eps, last_only ? 1 : 0, p.R, hid, c->st));
+    CK(rmsnorm_launch(h, md.gf, w.u32, w.uh, w.ul, rows, D, k.rms_eps, last_only && !compact ? 1 : 0,
+                      compact ? 1 : p.R, hid, c->st));
   }
   // Every head whose caller wants only row outputs takes the fused
   // epilogue: no logits reach memory.  Measured against writing the logits
@@ -918,6 +942,7 @@ int cdsl_prefill(cdsl_ctx* c, const int32_t* tokens, int32_t B, int32_t L, int32
     upload_table(c, px);
     CK(fill_int_launch(px->Lp, 0, B, c->st));
     CK(fill_int_launch(px->gen_len, 0, B, c->st));
+    CK(fill_int_launch(px->Lm1, L - 1, B, c->st));
     const int chunk = prefill_chunk_prompts(c->lim);
     for (int b0 = 0; b0 < B; b0 += chunk) {
       const int nb = std::min(chunk, B - b0);
@@ -940,7 +965,7 @@ int cdsl_prefill(cdsl_ctx* c, const int32_t* tokens, int32_t B, int32_t L, int32
       la.topk_lp = head_lp;
       la.topk_rows = c->iota + b0;
       run_pass(c, c->m[0], p, 0, 0, false, false, nullptr, true);
-      run_pass(c, c->m[1], p, 0, 0, true, true, nullptr, true, nullptr, 0, &la);
+      run_pass(c, c->m[1], p, 0, 0, true, true, nullptr, true, nullptr, 0, &la, px->Lm1);
     }
     CK(add_launch(B, nullptr, px->Lp, L, c->st));
     CK(last_tokens_launch(B, tokens, L, px->ptail, c->st));
