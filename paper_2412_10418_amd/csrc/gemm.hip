@@ -170,9 +170,10 @@ __global__ void split_planes(const float* __restrict__ x, bf16* __restrict__ hi,
 // MI355X (1 to 4096 rows, the projections and heads of 1B to 7B models, every
 // split; weights from HBM), in us.  occ workgroups share a CU, so a round
 // holds 256 * occ of them; a round of n workgroups of `per` stages takes
-//   round + per * sqrt(lone^2 + (full * n / (256 * occ))^2),
+//   round + per * sqrt(lone^2 + (full * n / (256 * occ))^2 + (fill * c)^2),
 // lone the stage time of a workgroup by itself (latency), full the growth
-// when every slot is taken (matrix cores and L2 shared, lower clocks).  Over
+// when every slot is taken (matrix cores shared, lower clocks), c the time of
+// the round's copies into LDS at 12.5 TB/s (rows past M are not read).  Over
 // those shapes the model's choice is on average 2% slower than the best
 // measured (configuration, split) pair; these eleven configurations together
 // are within 1% of the best of the 26 that were timed.
@@ -189,19 +190,19 @@ constexpr int kShape[kGemmCfgs][2] = {CDSL_GEMM_CFGS(CFG_SHAPE)};
 #undef CFG_SHAPE
 constexpr struct {
   int occ;
-  float start, round, lone, full;
+  float start, round, lone, full, fill;
 } kCost[] = {
-    {1, 6.4f, 6.8f, 1.52f, 2.51f},   // 256 x 256
-    {1, 5.5f, 5.2f, 1.06f, 1.67f},   // 160 x 256
-    {1, 5.3f, 4.4f, 0.86f, 1.37f},   // 128 x 256
-    {1, 4.8f, 4.1f, 0.59f, 0.92f},   // 160 x 128
-    {1, 4.5f, 3.5f, 0.46f, 0.76f},   // 128 x 128
-    {1, 4.6f, 3.4f, 0.54f, 0.76f},   // 64 x 256
-    {1, 3.5f, 2.4f, 0.38f, 0.45f},   // 64 x 128
-    {2, 3.4f, 1.7f, 0.23f, 0.68f},   // 64 x 64
-    {2, 3.0f, 1.3f, 0.24f, 0.76f},   // 48 x 64
-    {3, 3.3f, 0.7f, 0.18f, 0.93f},   // 32 x 64
-    {3, 3.0f, 0.5f, 0.18f, 0.79f},   // 16 x 64
+    {1, 6.8f, 6.7f, 1.51f, 0.74f, 1.29f},   // 256 x 256
+    {1, 5.7f, 5.2f, 1.04f, 0.68f, 1.08f},   // 160 x 256
+    {1, 5.4f, 4.5f, 0.86f, 0.86f, 0.82f},   // 128 x 256
+    {1, 5.0f, 4.1f, 0.58f, 0.47f, 0.73f},   // 160 x 128
+    {1, 4.5f, 3.6f, 0.47f, 0.46f, 0.63f},   // 128 x 128
+    {1, 4.6f, 3.4f, 0.54f, 0.76f, 0.00f},   // 64 x 256
+    {1, 3.6f, 2.4f, 0.37f, 0.23f, 0.62f},   // 64 x 128
+    {2, 3.6f, 1.6f, 0.23f, 0.47f, 0.53f},   // 64 x 64
+    {2, 3.0f, 1.3f, 0.24f, 0.35f, 0.87f},   // 48 x 64
+    {3, 3.2f, 0.8f, 0.18f, 0.23f, 0.95f},   // 32 x 64
+    {3, 3.1f, 0.5f, 0.18f, 0.26f, 0.97f},   // 16 x 64
 };
 static_assert(sizeof(kCost) / sizeof(kCost[0]) == kGemmCfgs, "a cost per configuration");
 constexpr double kPlaneRate = 5e6;   // bytes per us of split planes (written, then read by the fold)
@@ -220,11 +221,14 @@ struct Plan {
 // launch of their own (kReduce); kNone: no split.
 enum SplitUse { kFold = 0, kReduce = 1, kNone = 2 };
 
-double cfg_us(int cfg, int tiles, int splits, int per) {
+double cfg_us(int cfg, int rows, int tiles, int splits, int per) {
   const auto& c = kCost[cfg];
   const int n = tiles * splits, cap = 256 * c.occ, full = n / cap, rem = n % cap;
-  auto round = [&](double f) { return c.round + per * sqrt((double)c.lone * c.lone + (c.full * f) * (c.full * f)); };
-  return c.start + full * round(1.0) + (rem ? round((double)rem / cap) : 0.0);
+  auto round = [&](int k) {
+    const double f = c.full * k / cap, m = c.fill * (2 * rows + kShape[cfg][1]) * (2.0 * DKC) * k / 12.5e6;
+    return c.round + per * sqrt((double)c.lone * c.lone + f * f + m * m);
+  };
+  return c.start + full * round(cap) + (rem ? round(rem) : 0.0);
 }
 
 // The plan of a shape: a pure function of its arguments.  hd > 0: only
@@ -254,7 +258,7 @@ Plan search_plan(int M, int N, int K, SplitUse use, int hd, size_t max_ws) {
       last = ks;
       const double plane = (double)M16 * N * 4.0;
       if (ks > 1 && ks * ((double)M * N * 4.0) > (double)max_ws) break;
-      double us = std::max(cfg_us(c, tiles, ks, per), stream);
+      double us = std::max(cfg_us(c, M16 / (int)tm, tiles, ks, per), stream);
       if (ks > 1) us += (use == kReduce ? 4.5 : 2.0) + (ks + 1) * plane / kPlaneRate;
       if (us < p.us) {
         p.us = us;
@@ -315,15 +319,17 @@ int gemm_rowstats_tiles(int M, int N, int K, int dtype) {
 }
 
 // The rotary epilogue needs an unsplit launch of tiles with whole heads.  It
-// costs about what the separate rotary launch does when the grid is small
-// (80 rows x 3072 columns: 20.5 us, against 9.5 us split in four and a 5.6 us
-// rotary launch that folds the planes), and saves the product's trip through
-// memory when it is large; a split's planes are in the plan's time already.
+// takes 3 to 14 us more than the stores' (80 x 3072: 15.7 us in all, against
+// 9.4 split in four and 5.4 for the rotary launch that folds the planes; 800
+// x 12288: 139, against 126 and a launch that reads the 39 MB product), and
+// saves the rotary launch and the product's trip through memory.  So it is
+// taken where the projection is best not split anyway, and where a split
+// (whose planes are in its plan's time) gains less than 2 us.
 bool gemm_rope_fusable(int M, int N, int K, int dtype, int hd) {
   if (M <= 0 || dtype != 1 || (hd != 64 && hd != 128) || N % hd != 0) return false;
   const Plan f = make_plan(M, N, K, dtype, kNone, hd), s = make_plan(M, N, K, dtype, kFold);
   if (f.us > 1e200) return false;
-  return f.us <= s.us + 0.5 + (s.ksplit == 1 ? 2.0 * M * (double)N * 4.0 / kPlaneRate : 0.0);
+  return f.us <= s.us + (s.ksplit == 1 ? 1.0 + 2.0 * M * (double)N * 4.0 / kPlaneRate : -2.0);
 }
 
 int gemm_check(int M, int N, int K, int dtype) {
@@ -380,6 +386,7 @@ hipError_t gemm_launch(const GemmOperand& A, const void* B, const GemmOut& out, 
   a.kchunk = p.kchunk;
   a.tiles_m = p.tiles_m;
   a.tiles_n = p.tiles_n;
+  a.band = p.tiles_m <= 8 ? p.tiles_m : 4;
   a.partial = (float*)ws;
   a.rs = stats ? *rs : RowStats{};
   a.re = rope ? *rope : RopeEpi{};

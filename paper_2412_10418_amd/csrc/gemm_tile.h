@@ -38,6 +38,7 @@ struct GemmArgs {
   int ksplit, kchunk;
   float* partial;   // split planes [ksplit][M][N]
   int tiles_m, tiles_n;
+  int band;         // row blocks per band of the tile order
   RowStats rs;      // kEpiRowStats: per-tile row statistics instead of C
   RopeEpi re;       // kEpiRope: rotary + KV write instead of C
 };
@@ -60,7 +61,6 @@ struct GemmArgs {
 constexpr int kGemmCfgs = 11;
 constexpr int DBK = 32;         // K granularity (one MFMA k-step)
 constexpr int DKC = 64;         // K per stage
-constexpr int kDenseBand = 8;   // row blocks per band of the tile order
 
 // The kernels by use, each in its own file (and under its own name in a
 // profile): passes of more than 128 rows, prompt prefill, passes of at most
@@ -525,15 +525,17 @@ __device__ __forceinline__ void gemm_bf16(const GemmArgs& a) {
   const int lr = lane & 15, lg = lane >> 4;
   // XCD-aware tile order.  Workgroups are dispatched round-robin over the 8
   // XCDs (each with its own L2), so workgroup p runs on XCD p % 8.  Give each
-  // XCD a contiguous range of logical tiles, ordered in bands of up to 8 row
-  // blocks with the row block fastest: the tiles an XCD runs together then
+  // XCD a contiguous range of logical tiles, ordered in bands of a.band row
+  // blocks (all of up to 8, else 4: an XCD's 32 tiles are then 4 x 8, which
+  // read the fewest rows of two planes and columns of one; 4096 x 22016 x
+  // 4096: 1236 us, 1263 with bands of 8) with the row block fastest: the tiles an XCD runs together then
   // share weight column blocks and activation row blocks through its L2.
   const int T = a.tiles_m * a.tiles_n;
   const int p = blockIdx.x, xcd = p & 7, slot = p >> 3;
   const int per = T >> 3, rem = T & 7;
   const int tile = xcd < rem ? xcd * (per + 1) + slot : rem * (per + 1) + (xcd - rem) * per + slot;
-  const int band = tile / (kDenseBand * a.tiles_n), b0 = band * kDenseBand;
-  const int bh = min(kDenseBand, a.tiles_m - b0), in = tile - b0 * a.tiles_n;
+  const int band = tile / (a.band * a.tiles_n), b0 = band * a.band;
+  const int bh = min(a.band, a.tiles_m - b0), in = tile - b0 * a.tiles_n;
   const int tm_blk = b0 + in % bh, tn_blk = in / bh;
   const int m0 = tm_blk * BM, n0 = tn_blk * BN;
   const int kbeg = blockIdx.z * a.kchunk;
