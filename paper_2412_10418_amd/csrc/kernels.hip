@@ -1288,18 +1288,33 @@ __global__ __launch_bounds__(256) void rowstats_merge_kernel(RowStats s, LogitAr
   const int dst = a.topk_rows ? a.topk_rows[m] : m;
   const int nc = s.tiles * s.kk;
   const long long cb = base * s.kk;
+  // the candidates stay in registers where they fit (up to 2048)
+  constexpr int NC = 8;
+  const bool held = nc <= 256 * NC;
+  float hv[NC];
+  int hi[NC];
+#pragma unroll
+  for (int e = 0; e < NC; ++e) {
+    const int q = tid + 256 * e;
+    hv[e] = held && q < nc ? s.tv[cb + q] : -INFINITY;
+    hi[e] = held && q < nc ? s.tc[cb + q] : 0x7fffffff;
+  }
   float pv = INFINITY;
   int pi = -1;
   for (int r = 0; r < a.kk; ++r) {
     float cv = -INFINITY;
     int ci = 0x7fffffff;
-    for (int q = tid; q < nc; q += 256) {
-      const float v = s.tv[cb + q];
-      const int id = s.tc[cb + q];
+    auto take = [&](float v, int id) {
       if ((v < pv || (v == pv && id > pi)) && vi_better(v, id, cv, ci)) {
         cv = v;
         ci = id;
       }
+    };
+    if (held) {
+#pragma unroll
+      for (int e = 0; e < NC; ++e) take(hv[e], hi[e]);
+    } else {
+      for (int q = tid; q < nc; q += 256) take(s.tv[cb + q], s.tc[cb + q]);
     }
     float fv;
     int fi;
