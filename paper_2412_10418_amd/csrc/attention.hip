@@ -692,14 +692,31 @@ AttnPlan attn_plan(const PassDesc& p, int H, int Hkv, int hd, int dtype, int max
   }
   const int rtw = pl.threads / 64 / pl.kw * pl.rpw;
   pl.row_groups = (pl.row_tiles + rtw - 1) / rtw;
-  // enough workgroups for two per CU, >= 1 key-block pair per split, and at
-  // most kAttnMaxList key blocks per split; no split (and no combine
-  // launch) when the grid already holds two workgroups per CU or when a
-  // workgroup's chain of pair iterations is short
+  // Key splits.  None where the grid already holds two workgroups per CU or a
+  // workgroup's chain of pair iterations is short.  Else the split with the
+  // least rounds x (iterations + 3): a round holds one or two workgroups per
+  // CU (128 KB or 64 KB of LDS, two waves per SIMD), and a workgroup's start
+  // (row data, block list, first pair) and end take about three iterations; a
+  // split adds the combine launch.  16 prompts x 8 KV heads x 2048 keys: the
+  // rollout's 128 workgroups in two splits (one round) 33 us, in eight 52; the
+  // verification's in four 76 us, in eight 93.  At least one key-block pair
+  // and at most kAttnMaxList key blocks per split.
   const int base = p.nb * Hkv * pl.row_groups;
-  const int iters1 = ((nK + 1) / 2 + pl.kw - 1) / pl.kw;
-  int s = (base >= 512 || iters1 <= 8) ? 1 : (1024 + base - 1) / base;
-  s = std::min(s, (nK + 1) / 2);
+  const int pairs = (nK + 1) / 2, iters1 = (pairs + pl.kw - 1) / pl.kw;
+  const int smax = std::max(1, std::min({max_splits, kAttnMaxSplits, pairs}));
+  int s = 1;
+  if (base < 512 && iters1 > 8) {
+    const int slots = 256 * (pl.threads == 256 && pl.kw == 1 ? 2 : 1);
+    double best = 1e300;
+    for (int c = 1; c <= smax; ++c) {
+      const int it = ((pairs + c - 1) / c + pl.kw - 1) / pl.kw;
+      const double t = (double)((base * c + slots - 1) / slots) * (it + 3) + (c > 1 ? 1.5 + 0.1 * c : 0.0);
+      if (t < best) {
+        best = t;
+        s = c;
+      }
+    }
+  }
   s = std::max(s, (nK + kAttnMaxList - 1) / kAttnMaxList);
   s = std::max(1, std::min(s, std::min(max_splits, kAttnMaxSplits)));
   int bps = (nK + s - 1) / s;
