@@ -114,8 +114,8 @@ __device__ __forceinline__ void part_store(const GemmArgs& a, int row, int col, 
 // column tile's index in the RowStats layout.
 //
 // This pass is VALU-bound (one 160 x 256 tile took about 27 us when every
-// place scanned the whole run in registers; see the LM head's figures at
-// dense_cfgs).
+// place scanned the whole run in registers; the 800-row head of 32000 tokens
+// with five places went from 455 to 368 us, planes and merge included).
 template <int NT, int BM, int BN>
 struct RsLayout {
   static constexpr int CW = BN / 4;                                     // columns per lane
