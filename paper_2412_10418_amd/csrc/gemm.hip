@@ -295,7 +295,7 @@ double cfg_us(int cfg, int rows, int tiles, int splits, int per) {
 Plan search_plan(int M, int N, int K, SplitUse use, int hd, size_t max_ws) {
   Plan p{};
   p.kind = M <= 128 ? 1 : 0;
-  const int M16 = (M + 15) / 16 * 16, nk = (K + DKC - 1) / DKC;
+  const int M16 = (M + 15) / 16 * 16, nk = (K - 1) / DKC + 1;
   // weights once from HBM, whatever the tiles
   const double stream = 3.0 + (double)N * K * 2.0 / 4.9e6;
   p.us = 1e300;
@@ -323,7 +323,7 @@ Plan search_plan(int M, int N, int K, SplitUse use, int hd, size_t max_ws) {
         p.tiles_m = (int)tm;
         p.tiles_n = (int)tn;
         p.ksplit = ks;
-        p.kchunk = per * DKC;
+        p.kchunk = (int)std::min<long long>((long long)per * DKC, K);
       }
     }
   }
@@ -449,10 +449,12 @@ hipError_t gemm_launch(const GemmOperand& A, const void* B, const GemmOut& out, 
   a.re = rope ? *rope : RopeEpi{};
   const int variant = stats ? 1 : rope ? 2 : 0;
   const dim3 grid(p.tiles_m * p.tiles_n, 1, p.ksplit);
-  // the copies into LDS move whole 16-byte chunks: operands that are not
-  // aligned so (a caller's own; the library's always are) go through registers
-  const bool aligned = (((uintptr_t)A.hi | (uintptr_t)A.lo | (uintptr_t)B) & 15) == 0;
-  if (!aligned) {
+  // the copies into LDS move whole 16-byte chunks at 32-bit offsets within a
+  // tile: operands that are not aligned so, or whose tile of the larger side
+  // spans 2 GiB (a caller's own; the library's are neither), go through registers
+  const long long span = (long long)std::max(kShape[p.cfg][0], kShape[p.cfg][1]) * K * 2;
+  const bool direct = (((uintptr_t)A.hi | (uintptr_t)A.lo | (uintptr_t)B) & 15) == 0 && span < (1LL << 31);
+  if (!direct) {
     if (variant == 2) return hipErrorInvalidValue;
     gemm_unaligned_kernels(p.cfg, variant, grid, a, st);
   } else if (p.kind == 1) {

@@ -68,7 +68,8 @@ constexpr int DKC = 64;         // K per stage
 void gemm_dense_kernels(int cfg, int epi, dim3 grid, const GemmArgs& a, hipStream_t st);
 void gemm_prefill_kernels(int cfg, int epi, dim3 grid, const GemmArgs& a, hipStream_t st);
 void gemm_skinny_kernels(int cfg, int epi, dim3 grid, const GemmArgs& a, hipStream_t st);
-// operands that are not 16-byte aligned (epi 0 and 1)
+// operands that the direct copies do not take: not 16-byte aligned, or a tile
+// that spans 2 GiB (epi 0 and 1)
 void gemm_unaligned_kernels(int cfg, int epi, dim3 grid, const GemmArgs& a, hipStream_t st);
 
 namespace {
@@ -511,8 +512,9 @@ __device__ __forceinline__ void sched_step() {
 // EPI: 0 the stores (product, residual, SwiGLU, split planes), 1
 // kEpiRowStats, 2 kEpiRope (each its own kernel, so that the registers of an
 // epilogue do not weigh on the others).
-// DMA: the copies go from memory straight into LDS (16-byte aligned operands);
-// else through registers.
+// DMA: the copies go from memory straight into LDS (16-byte aligned operands
+// whose tiles span less than 2 GiB: buffer offsets are 32-bit and the upper
+// half marks lanes that read nothing); else through registers.
 template <int WM, int WN, int TM, int TN, int P, int EPI, bool DMA = true>
 __device__ __forceinline__ void gemm_bf16(const GemmArgs& a) {
   using C = DenseCfg<WM, WN, TM, TN, P>;
@@ -539,8 +541,8 @@ __device__ __forceinline__ void gemm_bf16(const GemmArgs& a) {
   const int tm_blk = b0 + in % bh, tn_blk = in / bh;
   const int m0 = tm_blk * BM, n0 = tn_blk * BN;
   const int kbeg = blockIdx.z * a.kchunk;
-  const int klen = min(a.K, kbeg + a.kchunk) - kbeg;
-  const int nk = (klen + DKC - 1) / DKC;
+  const int klen = min(a.K - kbeg, a.kchunk);
+  const int nk = (int)(((unsigned)klen + DKC - 1) / DKC);
 
   // copies: KB q of a unit is rows 8q .. 8q + 7; lane l reads row l / 8,
   // chunk (l % 8) ^ (l / 8) of it
@@ -551,23 +553,26 @@ __device__ __forceinline__ void gemm_bf16(const GemmArgs& a) {
   const bf16* hi0 = a.Ahi + (long long)m0 * a.K + kbeg;
   const bf16* lo0 = a.Alo + (long long)m0 * a.K + kbeg;
   const bf16* w0 = a.B + (long long)n0 * a.K + kbeg;
-  const unsigned a_rec = (unsigned)min(BM, a.M - m0) * row_b - kbeg * 2;
-  const unsigned w_rec = (unsigned)min(BN, a.N - n0) * row_b - kbeg * 2;
-  auto copy = [&](const bf16* base, unsigned rec, int t, int dst, auto np_c, auto nb_c) __attribute__((always_inline)) {
+  // what the copies are checked against: bytes from the unit's base (DMA), or rows
+  const unsigned a_lim = (unsigned)min(BM, a.M - m0) * (DMA ? row_b : 1u) - (DMA ? kbeg * 2 : 0);
+  const unsigned w_lim = (unsigned)min(BN, a.N - n0) * (DMA ? row_b : 1u) - (DMA ? kbeg * 2 : 0);
+  auto copy = [&](const bf16* base, unsigned lim, int t, int dst, auto np_c, auto nb_c) __attribute__((always_inline)) {
     constexpr int np = decltype(np_c)::value, nb = decltype(nb_c)::value;   // copies per wave, 1 KB blocks of the unit
     if constexpr (!DMA) {
+      // 64-bit addresses, rows and columns compared as such
+      const int k = t * DKC + chunk * 8;
 #pragma unroll
       for (int u = 0; u < np; ++u) {
         if (wave + NW * u >= nb) continue;
-        const unsigned off = (t == nk - 1 ? voff | half : voff) + (unsigned)(NW * 8 * u) * row_b;
+        const unsigned r = (wave + NW * u) * 8 + (lane >> 3);
         u32x4 x = {0u, 0u, 0u, 0u};
-        if (t < nk && off < rec - (unsigned)t * (DKC * 2)) x = *(const u32x4*)((const char*)(base + (long long)t * DKC) + off);
+        if (t < nk && r < lim && k < klen) x = *(const u32x4*)(base + (long long)r * a.K + k);
         *(u32x4*)(lds + dst + (wave + NW * u) * 1024 + lane * 16) = x;
       }
       return;
     }
     __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(base + (long long)t * DKC), 0, t < nk ? rec - (unsigned)t * (DKC * 2) : 0u, 0x00020000);
+        (void*)(base + (long long)t * DKC), 0, t < nk ? lim - (unsigned)t * (DKC * 2) : 0u, 0x00020000);
     const unsigned vo = t == nk - 1 ? voff | half : voff;
 #pragma unroll
     for (int u = 0; u < np; ++u) {
@@ -578,10 +583,10 @@ __device__ __forceinline__ void gemm_bf16(const GemmArgs& a) {
     }
   };
   auto copy_w = [&](int t, int slot) __attribute__((always_inline)) {
-    copy(w0, w_rec, t, slot * C::WU, ic<C::CW>{}, ic<BN / 8>{});
+    copy(w0, w_lim, t, slot * C::WU, ic<C::CW>{}, ic<BN / 8>{});
   };
   auto copy_a = [&](const bf16* base, int t, int slot) __attribute__((always_inline)) {
-    copy(base, a_rec, t, (P + 1) * C::WU + slot * C::AU, ic<C::CA>{}, ic<BM / 8>{});
+    copy(base, a_lim, t, (P + 1) * C::WU + slot * C::AU, ic<C::CA>{}, ic<BM / 8>{});
   };
   // waits until at most nw W units and na A units of this wave's copies, the
   // youngest, are outstanding, and for its LDS reads; then the barrier

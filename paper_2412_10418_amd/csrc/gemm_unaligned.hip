@@ -1,5 +1,6 @@
-// bf16 projection kernels for operands that are not 16-byte aligned (only the
-// kernel-level entry points take such).
+// bf16 projection kernels for operands that the direct copies do not take: not
+// 16-byte aligned, or with a tile that spans 2 GiB (only the kernel-level entry
+// points take such).
 #include "gemm_tile.h"
 
 #define CASE(I, E, WM, WN, ...)                                                         \

@@ -53,6 +53,22 @@ def test_projection_with_unaligned_weights(M, N, K, skew):
     assert torch.equal(cdsl_op_gemm(a, moved), cdsl_op_gemm(a, w))
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 64, 1 << 25), (33, 64, (1 << 24) + 32), (64, 3, 1 << 25)])
+def test_projection_over_tiles_beyond_two_gib(M, N, K):
+    """Rows so long that a tile of either operand spans 2 GiB or more.  Tolerance: a split sums at most K / 32 MFMA
+    steps per plane in fp32, each off by 2^-24 of the running sum: 2^-24 sqrt(2 K / 32), below 1e-4, in units of
+    the outputs' size."""
+    from paper_2412_10418_amd.binding import cdsl_op_gemm
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    a = torch.empty((M, K), device="cuda").normal_(0.0, 1.0, generator=g)
+    w = torch.empty((N, K), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g)
+    ref = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    for k in range(0, K, 1 << 22):
+        ref += torch.matmul(a[:, k:k + (1 << 22)].double(), w[:, k:k + (1 << 22)].double().t())
+    got = cdsl_op_gemm(a, w)
+    assert float((got.double() - ref).abs().max() / ref.abs().max()) < 1e-4
+
+
 @pytest.mark.parametrize("M,V,K,kk", [(1, 1000, 64, 16), (16, 32000, 1024, 5), (48, 4099, 96, 3), (80, 32000, 512, 0),
                                       (128, 1030, 256, 8), (161, 2000, 1024, 5), (300, 50257, 160, 2)])
 def test_head_rows_over_the_tile_shapes(M, V, K, kk):
