@@ -11,6 +11,55 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
+def _us(f, n=8, runs=9):
+    """The median over runs of n calls' GPU time per call, enqueued behind a busy stream."""
+    ts = []
+    f()
+    for _ in range(runs):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(2000000)
+        a.record()
+        for _ in range(n):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        ts.append(a.elapsed_time(b) * 1e3 / n)
+    return sorted(ts)[runs // 2]
+
+
+@pytest.mark.parametrize("M,V,K", [(1, 128256, 1024), (24, 128256, 1024), (16, 50257, 2048)])
+def test_head_places_cost_little_beside_the_product(M, V, K):
+    """Eight places of the top-k are one round over the tiles' lists, not eight: at these few rows the head with them
+    takes at most 1.8 times the head without (8 rounds that read every list again took 2.8 times)."""
+    from paper_2412_10418_amd.binding import cdsl_op_lm_head_rows
+    g = torch.Generator(device="cuda").manual_seed(V)
+    a = torch.randn((M, K), generator=g, device="cuda")
+    w = torch.empty((V, K), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g)
+    ids = torch.zeros(M, dtype=torch.int32, device="cuda")
+    assert _us(lambda: cdsl_op_lm_head_rows(a, w, ids, 8)) < 1.8 * _us(lambda: cdsl_op_lm_head_rows(a, w, ids, 0))
+
+
+@pytest.mark.parametrize("kk", [1, 7, 16])
+@pytest.mark.parametrize("every", [1, 16, 786])
+def test_head_places_with_the_best_entries_in_few_tiles(kk, every):
+    """The columns of every every-th tile of 64 are raised far above the rest: the best entries lie in all tiles, in
+    those of one sixteenth of the merge's threads (more than its list holds at kk = 16), or in one."""
+    from paper_2412_10418_amd.binding import cdsl_op_lm_head_rows
+    M, V, K = 5, 50257, 256
+    g = torch.Generator(device="cuda").manual_seed(kk)
+    a = 1.0 + 0.1 * torch.randn((M, K), generator=g, device="cuda")
+    w = torch.empty((V, K), device="cuda").normal_(0.0, 0.02, generator=g)
+    w[(torch.arange(V, device="cuda") // 64) % every == 3 % every] += 0.25
+    w = w.bfloat16()
+    lp, amax, ids, tlp = cdsl_op_lm_head_rows(a, w, torch.zeros(M, dtype=torch.int32, device="cuda"), kk)
+    lsm = torch.matmul(a.double(), w.double().t()).log_softmax(-1)
+    ref = lsm.topk(kk, -1).values
+    assert float((tlp.double() - ref).abs().max()) < 1e-4
+    assert float((lsm.gather(-1, ids.long()) - ref).abs().max()) < 1e-4
+    assert all(len(set(r)) == kk for r in ids.tolist())
+    assert torch.equal(amax, ids[:, 0])
+
+
 def _order(row, k):
     """The k best ids: value descending, id ascending, NaN never."""
     ids = np.flatnonzero(~np.isnan(row))
