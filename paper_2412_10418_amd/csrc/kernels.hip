@@ -330,42 +330,50 @@ __device__ __forceinline__ int vocab_id(int id, int V) { return (id >= 0 && id <
 
 // The kk best entries (value descending, id ascending) of a row whose entries
 // are spread over a workgroup's threads, in one round whatever kk <= 16 is:
-// each thread offers its best entry, sixteen groups of threads (by tid % 16)
-// keep theirs, and the kk-th best of those bounds the kk-th best of the row.
-// The entries at or above the bound are collected (about kk ln kk of them for
-// values in no order) and ranked by counting.
+// each thread offers its best entry, 32 groups of threads (by tid % 32) keep
+// theirs, and the kk-th best of those bounds the kk-th best of the row.  The
+// entries at or above the bound are collected (for values in no order about
+// 32 ln(32 / (32 - kk)): 5 at five places, 22 at sixteen; sixteen groups let
+// through 54 at sixteen places, and often twice that) and ranked by counting.
 constexpr int kTopList = 512;   // entries that a workgroup collects at most
+constexpr int kTopGroups = 32;
 constexpr int kNoId = 0x7fffffff;
 
 template <int NW>
 struct TopShared {
-  float gv[NW][16];
-  int gi[NW][16];
+  float gv[NW][kTopGroups];
+  int gi[NW][kTopGroups];
   int n;
   float v[kTopList];
   int id[kTopList];
 };
 
-template <int O>
-__device__ __forceinline__ void row_rank(float v, int i, int& rank) {
-  // the entry of the lane O places on, around a row of 16 lanes
-  const float ov = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + O, 0xF, 0xF, true));
-  const int oi = __builtin_amdgcn_mov_dpp(i, 0x120 + O, 0xF, 0xF, true);
-  rank += vi_better(ov, oi, v, i) ? 1 : 0;
-  if constexpr (O < 15) row_rank<O + 1>(v, i, rank);
+// rank += how many of a row of 16 lanes hold a better entry than (v, i),
+// each lane holding (ov, oi)
+template <int O = 0>
+__device__ __forceinline__ void row_rank(float ov, int oi, float v, int i, int& rank) {
+  float rv = ov;
+  int ri = oi;
+  if constexpr (O > 0) {
+    rv = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(ov), 0x120 + O, 0xF, 0xF, true));
+    ri = __builtin_amdgcn_mov_dpp(oi, 0x120 + O, 0xF, 0xF, true);
+  }
+  rank += vi_better(rv, ri, v, i) ? 1 : 0;
+  if constexpr (O < 15) row_rank<O + 1>(ov, oi, v, i, rank);
+}
+
+__device__ __forceinline__ void xor_best(int o, float& v, int& id) {
+  const float ov = __shfl_xor(v, o, 64);
+  const int oi = __shfl_xor(id, o, 64);
+  if (vi_better(ov, oi, v, id)) v = ov, id = oi;
 }
 
 // before the barrier: this thread's best entry (id kNoId: none)
 template <int NW>
 __device__ __forceinline__ void top_offer(float v, int id, TopShared<NW>& t) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 16; o < 64; o <<= 1) {
-    const float ov = __shfl_xor(v, o, 64);
-    const int oi = __shfl_xor(id, o, 64);
-    if (vi_better(ov, oi, v, id)) v = ov, id = oi;
-  }
-  if (lane < 16) {
+  xor_best(32, v, id);
+  if (lane < kTopGroups) {
     t.gv[w][lane] = v;
     t.gi[w][lane] = id;
   }
@@ -377,38 +385,41 @@ __device__ __forceinline__ void top_offer(float v, int id, TopShared<NW>& t) {
 // best value
 template <int NW>
 __device__ __forceinline__ void top_bound(const TopShared<NW>& t, int kk, float& bv, int& bi, float& best) {
-  const int lane = threadIdx.x & 63, j = lane & 15;
+  const int lane = threadIdx.x & 63, j = lane & 31;
   float v = -INFINITY;
   int id = kNoId;
 #pragma unroll
-  for (int w0 = 0; w0 < NW; w0 += 4) {
-    const int w = w0 + (lane >> 4);
+  for (int w0 = 0; w0 < NW; w0 += 2) {
+    const int w = min(w0 + (lane >> 5), NW - 1);
     const float ov = t.gv[w][j];
     const int oi = t.gi[w][j];
     if (vi_better(ov, oi, v, id)) v = ov, id = oi;
   }
-#pragma unroll
-  for (int o = 16; o < 64; o <<= 1) {
-    const float ov = __shfl_xor(v, o, 64);
-    const int oi = __shfl_xor(id, o, 64);
-    if (vi_better(ov, oi, v, id)) v = ov, id = oi;
-  }
-  id = min(id, kNoId - 16 + j);   // groups without an entry differ
+  if (NW > 1) xor_best(32, v, id);
+  id = min(id, kNoId - kTopGroups + j);   // groups without an entry differ
   int rank = 0;
-  row_rank<1>(v, id, rank);
+  row_rank(v, id, v, id, rank);
+  row_rank(__shfl_xor(v, 16, 64), __shfl_xor(id, 16, 64), v, id, rank);
   const int at = __builtin_ctzll(__ballot(rank == kk - 1)), first = __builtin_ctzll(__ballot(rank == 0));
   bv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), at));
   bi = __builtin_amdgcn_readlane(id, at);
   best = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), first));
 }
 
-template <int NW>
-__device__ __forceinline__ void top_push(float v, int id, TopShared<NW>& t) {
-  const int at = atomicAdd(&t.n, 1);
-  if (at < kTopList) {
-    t.v[at] = v;
-    t.id[at] = id;
-  }
+// the entries of x whose bit of mask is set; id_of(e) is the id of x[e]
+template <int NW, int N, typename Id>
+__device__ __forceinline__ void top_push(const float (&x)[N], unsigned mask, Id id_of, TopShared<NW>& t) {
+  if (!mask) return;
+  int at = atomicAdd(&t.n, __popc(mask));
+#pragma unroll
+  for (int e = 0; e < N; ++e)
+    if (mask >> e & 1) {
+      if (at < kTopList) {
+        t.v[at] = x[e];
+        t.id[at] = id_of(e);
+      }
+      ++at;
+    }
 }
 
 // after the barrier that follows the pushes: put(place, value, id) for every
@@ -419,6 +430,7 @@ __device__ __forceinline__ void top_place(const TopShared<NW>& t, int n, int kk,
     const float v = t.v[i];
     const int id = t.id[i];
     int rank = 0;
+#pragma unroll 8
     for (int j = 0; j < n; ++j) rank += vi_better(t.v[j], t.id[j], v, id) ? 1 : 0;
     if (rank < kk) put(rank, v, id);
   }
@@ -430,11 +442,7 @@ __device__ __forceinline__ void top_place(const TopShared<NW>& t, int n, int kk,
 template <int NW>
 __device__ __forceinline__ void top_one(float& v, int& id, TopShared<NW>& t) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(v, o, 64);
-    const int oi = __shfl_xor(id, o, 64);
-    if (vi_better(ov, oi, v, id)) v = ov, id = oi;
-  }
+  for (int o = 32; o > 0; o >>= 1) xor_best(o, v, id);
   if ((threadIdx.x & 63) == 0) {
     t.gv[threadIdx.x >> 6][0] = v;
     t.gi[threadIdx.x >> 6][0] = id;
@@ -489,16 +497,19 @@ __device__ __forceinline__ void lse_add(const float (&x)[N], float cm, float& m,
   for (int e = 0; e < N; ++e) s += __builtin_amdgcn_exp2f((x[e] - mn) * kLog2e);
 }
 
-// the logsumexp of a workgroup's (m, s); every thread returns it
+// the logsumexp of a workgroup's (m, s): put before a barrier, then taken by
+// every thread
 template <int NW>
-__device__ __forceinline__ float block_lse(float m, float s, float (&sm)[NW], float (&ss)[NW]) {
+__device__ __forceinline__ void lse_put(float m, float s, float (&sm)[NW], float (&ss)[NW]) {
   const float wm = wave_max(m);
   const float ws = wave_sum(wm == -INFINITY ? s : s * __builtin_amdgcn_exp2f((m - wm) * kLog2e));
   if ((threadIdx.x & 63) == 0) {
     sm[threadIdx.x >> 6] = wm;
     ss[threadIdx.x >> 6] = ws;
   }
-  __syncthreads();
+}
+template <int NW>
+__device__ __forceinline__ float lse_take(const float (&sm)[NW], const float (&ss)[NW]) {
   float M = -INFINITY, t = 0.f;
 #pragma unroll
   for (int u = 0; u < NW; ++u) M = fmaxf(M, sm[u]);
@@ -510,21 +521,19 @@ __device__ __forceinline__ float block_lse(float m, float s, float (&sm)[NW], fl
 // Logits row statistics, one workgroup per row, one read of the row: online
 // logsumexp, argmax, top-kk.  Ordering: value descending, then id ascending.
 //
-// Bound by the read.  A thread keeps only the maximum of each of its GN
-// groups of columns (16 columns of every GN-th chunk); a place of the top-kk
-// is the best of the waves' bests, and only the wave that held it looks for
-// its next one: the lanes whose maximum is the wave's read that group again
-// (from L2) for the lowest id.  Before, every thread kept a sorted list of
-// the kk best: 512 rows of 50257, top-5, took 157 us.
-constexpr int kRowGroups = 8;
-
-template <int NT, bool LSE>
+// Bound by the read.  A thread keeps the maximum of each of its GN groups of
+// columns (16 columns of every GN-th chunk) and the first slot that holds its
+// best, which is what it offers; only the groups that reach the bound are read
+// again (from L2).  Places taken one by one, each with two dependent reads and
+// a round of the workgroup, cost 2 to 3 us apiece: 500 rows of 50257, top-5,
+// took 37 us, now 32; 20 rows of 1000, top-16, 58, now 11.
+template <int NT, bool LSE, bool ONE>   // ONE: kk <= 1
 __global__ __launch_bounds__(NT) void logit_rows_kernel(LogitArgs a) {
-  constexpr int NW = NT / 64, GN = kRowGroups;
-  __shared__ float sv[2][NW], sm[NW], ss[NW];
-  __shared__ int si[2][NW];
+  constexpr int NW = NT / 64, GN = 4;
+  __shared__ TopShared<NW> top;
+  __shared__ float sm[NW], ss[NW];
   const int row = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x;
   const float* z = a.logits + (long long)row * (a.ld ? a.ld : (long long)a.V);
   const RowSlots rs = row_slots(z, a.V, (int)((uintptr_t)z / 4 & 3));
   const int nc = (rs.slots + 4 * NT - 1) / (4 * NT);   // chunks of 4 slots per thread
@@ -539,115 +548,128 @@ __global__ __launch_bounds__(NT) void logit_rows_kernel(LogitArgs a) {
   };
   auto id_of = [&](int c, int e) { return 4 * (tid + NT * (4 * c + (e >> 2))) - rs.shift + (e & 3); };
 
-  float g[GN], m = -INFINITY, s = 0.f;
+  float g[GN], m = -INFINITY, s = 0.f, bv = -INFINITY;
+  int bs = kNoId;   // the first slot that holds this thread's best value bv
 #pragma unroll
   for (int u = 0; u < GN; ++u) g[u] = -INFINITY;
   for (int c0 = 0; c0 < nc; c0 += GN) {
 #pragma unroll
     for (int u = 0; u < GN; ++u) {
       if (c0 + u >= nc) break;
-      float x[16];
+      float x[16], sx[4];
       chunk(c0 + u, x);
-      float cm = x[0];
 #pragma unroll
-      for (int e = 1; e < 16; ++e) cm = fmaxf(cm, x[e]);
+      for (int i = 0; i < 4; ++i) sx[i] = fmaxf(fmaxf(x[4 * i], x[4 * i + 1]), fmaxf(x[4 * i + 2], x[4 * i + 3]));
+      float cm = fmaxf(fmaxf(sx[0], sx[1]), fmaxf(sx[2], sx[3]));
       cm = fmaxf(cm, -INFINITY);   // all NaN: -inf
       g[u] = fmaxf(g[u], cm);
+      if (cm > bv) {
+        bv = cm;
+        bs = tid + NT * (4 * (c0 + u) + (sx[0] == cm ? 0 : sx[1] == cm ? 1 : sx[2] == cm ? 2 : 3));
+      }
       if (LSE) lse_add(x, cm, m, s);
-      else if (u & 1) __builtin_amdgcn_sched_barrier(0);   // two chunks' loads in flight per wave
     }
   }
-  // this wave's best entry ordered after (pv, pi), which no entry outside the
-  // groups' maxima precedes
-  auto wave_best = [&](float pv, int pi, float& wv, int& wi) {
-    float tv = g[0];
-#pragma unroll
-    for (int u = 1; u < GN; ++u) tv = fmaxf(tv, g[u]);
-    wv = wave_max(tv);
-    int id = 0x7fffffff;
-    if (tv == wv) {
-#pragma unroll 1
-      for (int c = 0; c < nc; ++c) {
-        float gu = g[0];
-#pragma unroll
-        for (int u = 1; u < GN; ++u) gu = (c & (GN - 1)) == u ? g[u] : gu;
-        if (gu != wv) continue;
-        float x[16];
-        chunk(c, x);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int t = id_of(c, e);
-          if (x[e] == wv && t >= 0 && t < a.V && (wv < pv || t > pi)) id = min(id, t);
-        }
-      }
+  if (bv == -INFINITY) {
+    // nothing above -inf: the first whole slot with a -inf of the row itself
+    for (int q = tid; q < rs.slots && bs == kNoId; q += NT) {
+      float x[4];
+      rs.load(q, x);
+      const int id = 4 * q - rs.shift;
+      if (id >= 0 && id + 4 <= a.V && (x[0] == bv || x[1] == bv || x[2] == bv || x[3] == bv)) bs = q;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) id = min(id, __shfl_xor(id, o, 64));
-    wi = id;
-  };
-  // the best of the waves' bests in buffer b
-  auto block_best = [&](int b, float& bv, int& bi) {
-    bv = sv[b][0];
-    bi = si[b][0];
-#pragma unroll
-    for (int u = 1; u < NW; ++u)
-      if (vi_better(sv[b][u], si[b][u], bv, bi)) {
-        bv = sv[b][u];
-        bi = si[b][u];
-      }
-  };
-  float wv;
-  int wi;
-  wave_best(INFINITY, -1, wv, wi);
-  if (lane == 0) {
-    sv[0][w] = wv;
-    si[0][w] = wi;
   }
+  const int dst = a.topk_rows ? a.topk_rows[row] : row;
   float lse = 0.f;
-  if (LSE) lse = block_lse<NW>(m, s, sm, ss);
-  else __syncthreads();
-  float bv;
-  int bi;
-  block_best(0, bv, bi);
-  if (tid == 0 && a.amax) a.amax[rowmap_index(a.amax_map, row)] = vocab_id(bi, a.V);
-  if (!LSE) return;
-  if (a.lp && tid == 0) {
+  auto put = [&](int r, float v, int id) {
+    if (r == 0 && a.amax) a.amax[rowmap_index(a.amax_map, row)] = vocab_id(id, a.V);
+    if (!LSE || r >= a.kk) return;
+    a.topk_ids[(long long)dst * a.kk + r] = vocab_id(id, a.V);
+    a.topk_lp[(long long)dst * a.kk + r] = v - lse;
+  };
+  auto gather = [&]() {
+    if (!LSE || !a.lp || tid != 0) return;
     const int tok = a.gather_tok[rowmap_index(a.gather_map, row)];
     const bool in = tok >= 0 && tok < a.V;
     if (!in && a.bad) *a.bad = 1;
     a.lp[row] = in ? z[tok] - lse : __int_as_float(0x7fc00000);
-  }
-  if (a.kk == 0) return;
-  const int dst = a.topk_rows ? a.topk_rows[row] : row;
-  for (int r = 0; r < a.kk; ++r) {
-    if (r > 0) block_best(r & 1, bv, bi);
-    if (tid == 0) {
-      a.topk_ids[(long long)dst * a.kk + r] = vocab_id(bi, a.V);
-      a.topk_lp[(long long)dst * a.kk + r] = bv - lse;
-    }
-    if (r + 1 == a.kk) break;
-    if (wi == bi && bi != 0x7fffffff) {   // this wave held it (uniform)
-      const int q = (bi + rs.shift) >> 2, u0 = (q / (4 * NT)) & (GN - 1);
-      if (q % NT == tid) {
-        float gm = -INFINITY;
-#pragma unroll 1
-        for (int c = u0; c < nc; c += GN) {
-          float x[16];
-          chunk(c, x);
+  };
+  if (LSE) lse_put<NW>(m, s, sm, ss);
+  if constexpr (ONE) {
+    top_one<NW>(bv, bs, top);
+    if (LSE) lse = lse_take<NW>(sm, ss);
+    gather();
+    // the thread that read the slot finds the first of its four ids
+    if (tid == (bs == kNoId ? 0 : bs % NT)) {
+      int id = kNoId;
+      if (bs != kNoId) {
+        float x[4];
+        rs.load(bs, x);
 #pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (x[e] < bv || (x[e] == bv && id_of(c, e) > bi && id_of(c, e) < a.V)) gm = fmaxf(gm, x[e]);
+        for (int e = 3; e >= 0; --e) {
+          const int t = 4 * bs - rs.shift + e;
+          if (x[e] == bv && t >= 0 && t < a.V) id = t;
         }
-#pragma unroll
-        for (int u = 0; u < GN; ++u) g[u] = u == u0 ? gm : g[u];
       }
-      wave_best(bv, bi, wv, wi);
+      put(0, bv, id);
     }
-    if (lane == 0) {
-      sv[(r + 1) & 1][w] = wv;
-      si[(r + 1) & 1][w] = wi;
+    return;
+  }
+  top_offer<NW>(bv, bs, top);
+  __syncthreads();
+  if (LSE) lse = lse_take<NW>(sm, ss);
+  gather();
+  float cv, best;
+  int ci;
+  top_bound<NW>(top, a.kk, cv, ci, best);
+  // at least kk entries are above cv, or equal to it with an id up to ci
+  ci = ci >= kNoId - kTopGroups ? kNoId : 4 * ci + 3 - rs.shift;
+  if (bv >= cv) {
+#pragma unroll 1
+    for (int c = 0; c < nc; ++c) {
+      float gc = g[0];
+#pragma unroll
+      for (int u = 1; u < GN; ++u) gc = (c & (GN - 1)) == u ? g[u] : gc;
+      if (gc < cv || (gc == cv && id_of(c, 0) > ci)) continue;
+      float x[16];
+      chunk(c, x);
+      unsigned mask = 0;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int id = id_of(c, e);
+        mask |= ((x[e] > cv || (x[e] == cv && id <= ci)) && id >= 0 && id < a.V ? 1u : 0u) << e;
+      }
+      top_push<NW>(x, mask, [&](int e) { return id_of(c, e); }, top);
+    }
+  }
+  __syncthreads();
+  const int n = top.n;
+  if (n <= kTopList) {
+    top_place<NW>(top, n, a.kk, put);
+    return;
+  }
+  // more entries at the bound than the list holds (the best entries all with
+  // few threads): place by place
+  float pv = INFINITY;
+  int pi = -1;
+  for (int r = 0; r < a.kk; ++r) {
+    float v = -INFINITY;
+    int id = kNoId;
+#pragma unroll 1
+    for (int c = 0; c < nc; ++c) {
+      float x[16];
+      chunk(c, x);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int t = id_of(c, e);
+        if (t >= 0 && t < a.V && vi_better(pv, pi, x[e], t) && vi_better(x[e], t, v, id)) v = x[e], id = t;
+      }
     }
     __syncthreads();
+    top_one<NW>(v, id, top);
+    pv = v;
+    pi = id;
+    if (tid == 0) put(r, pv, pi);
   }
 }
 
@@ -763,8 +785,11 @@ __global__ __launch_bounds__(NT) void soft_rows_kernel(const float* __restrict__
     lse_add(x, cp, mp, sp);
     lse_add(y, cq, mq, sq);
   }
-  const float lp = block_lse<NW>(mp, sp, sm[0], ss[0]);
-  const float lq = block_lse<NW>(mq, sq, sm[1], ss[1]);
+  lse_put<NW>(mp, sp, sm[0], ss[0]);
+  lse_put<NW>(mq, sq, sm[1], ss[1]);
+  __syncthreads();
+  const float lp = lse_take<NW>(sm[0], ss[0]);
+  const float lq = lse_take<NW>(sm[1], ss[1]);
   // w of this thread's four ids of block b
   auto weights = [&](const float (&x)[4], const float (&y)[4], float (&t)[4]) __attribute__((always_inline)) {
 #pragma unroll
@@ -1378,14 +1403,12 @@ __global__ __launch_bounds__(NT) void rowstats_merge_kernel(RowStats s, LogitArg
     const float mx = s.mx[base + t];
     if (mx != -INFINITY) sv += s.se[base + t] * __expf(mx - G);
     if constexpr (!ONE) {
-      int id = s.am[base + t];
-      if (!reaches(mx, id)) continue;
-      top_push<NW>(mx, id, top);
-      for (int u = 1; u < s.kk; ++u) {
-        const float v = s.tv[(base + t) * s.kk + u];
-        id = s.tc[(base + t) * s.kk + u];
-        if (!reaches(v, id)) break;
-        top_push<NW>(v, id, top);
+      if (!reaches(mx, s.am[base + t])) continue;
+      for (int u = 0; u < s.kk; ++u) {
+        const float v[1] = {s.tv[(base + t) * s.kk + u]};
+        const int id = s.tc[(base + t) * s.kk + u];
+        if (!reaches(v[0], id)) break;
+        top_push<NW>(v, 1u, [&](int) { return id; }, top);
       }
     }
   }
@@ -1452,18 +1475,32 @@ hipError_t rowstats_merge_launch(const RowStats& s, const LogitArgs& a, int M, h
 hipError_t logit_rows_launch(const LogitArgs& a, int M, hipStream_t st) {
   if (M == 0) return hipSuccess;
   if (a.kk > 16 || a.kk < 0) return hipErrorInvalidValue;
-  // Long rows: 1024 threads where there are few (100 rows of 128256: 43
-  // against 64 us with 512), 512 where a CU has several (512 rows of 50257:
-  // 49 against 66 us).  Short rows: 256 threads (900 rows of 4001: 38 against
-  // 44 us).
-#define LOGIT_ROWS(NT)                                                   \
-  do {                                                                   \
-    if (a.want_lse) logit_rows_kernel<NT, true><<<M, NT, 0, st>>>(a);    \
-    else logit_rows_kernel<NT, false><<<M, NT, 0, st>>>(a);              \
+  // A chunk of four slots per thread, up to a limit: a row's time is its reads
+  // and the exchange between its waves, so few rows take all the threads they
+  // can fill and many rows share the CUs.  Us with 256 / 512 / 1024 threads:
+  // top-5, 384 rows of 50257 55 / 33 / 29, 900 of 32000 43 / 32 / 38, 900 of
+  // 128256 184 / 115 / 107; argmax, 20 rows of 16000 6.4 / 5.4 / 6.3, 200 of
+  // 50257 22 / 14 / 12, 384 23 / 17 / 19, 900 30 / 32 / 37.  900 rows of 1000,
+  // top-5, with 64 / 128 / 256: 9.3 / 10.1 / 11.4.
+  const bool one = a.kk <= 1 || !a.want_lse;
+  const int slots = a.V % 4 ? a.V / 4 + 2 : a.V / 4;
+  const int limit = one ? (M > 512 && a.V <= 65536 ? 256 : M <= 256 && a.V > 32768 ? 1024 : 512)
+                        : (M > 512 && a.V <= 65536 ? 512 : 1024);
+  int nt = 64;
+  while (nt < limit && 4 * nt < slots) nt *= 2;
+#define LOGIT_ROWS(NT)                                                                 \
+  do {                                                                                 \
+    if (!a.want_lse) logit_rows_kernel<NT, false, true><<<M, NT, 0, st>>>(a);          \
+    else if (one) logit_rows_kernel<NT, true, true><<<M, NT, 0, st>>>(a);        \
+    else logit_rows_kernel<NT, true, false><<<M, NT, 0, st>>>(a);                      \
   } while (0)
-  if (a.V <= 8192) LOGIT_ROWS(256);
-  else if (M >= 384) LOGIT_ROWS(512);
-  else LOGIT_ROWS(1024);
+  switch (nt) {
+    case 64: LOGIT_ROWS(64); break;
+    case 128: LOGIT_ROWS(128); break;
+    case 256: LOGIT_ROWS(256); break;
+    case 512: LOGIT_ROWS(512); break;
+    default: LOGIT_ROWS(1024);
+  }
 #undef LOGIT_ROWS
   return hipGetLastError();
 }

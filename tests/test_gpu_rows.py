@@ -67,7 +67,7 @@ def _order(row, k):
 
 
 @pytest.mark.parametrize("M,V", [(3, 5), (9, 64), (6, 1023), (5, 4097), (4, 8193), (3, 16387), (400, 8200), (2, 70001),
-                                 (2, 150001), (1, 300007)])
+                                 (2, 150001), (1, 300007), (7, 2041), (600, 20001)])
 @pytest.mark.parametrize("kk", [0, 1, 5, 16])
 def test_logit_rows_alignment_ties_and_infinities(M, V, kk):
     from paper_2412_10418_amd.binding import cdsl_op_logit_rows
@@ -99,6 +99,37 @@ def test_logit_rows_alignment_ties_and_infinities(M, V, kk):
         for u in range(kk):
             r = x[want[u]] - lse
             assert tl[m, u] == r or abs(tl[m, u] - r) < 2e-5
+
+
+@pytest.mark.parametrize("V", [20001, 128256])
+def test_logit_rows_with_the_best_entries_in_few_threads(V):
+    """Every entry of one slot of four in 32 (the slots of one group of threads) lies above all others: more entries
+    reach the bound than a workgroup lists."""
+    from paper_2412_10418_amd.binding import cdsl_op_logit_rows
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((6, V)).astype(np.float32)
+    z[:, np.arange(V) // 4 % 32 == 5] += 100.0
+    z[5] = np.round(z[5])
+    _, amax, tk, _ = (t.cpu().numpy() for t in
+                      cdsl_op_logit_rows(torch.from_numpy(z).cuda(), torch.zeros(6, dtype=torch.int32).cuda(), 16))
+    for m in range(6):
+        assert list(tk[m]) == list(_order(z[m], 16)) and amax[m] == tk[m, 0]
+
+
+@pytest.mark.parametrize("M,V", [(384, 128256), (900, 32000), (100, 1000)])
+def test_logit_rows_time_depends_on_neither_places_nor_values(M, V):
+    """Sixteen places are one round, not sixteen (which took 3.5 to 10 times as long as one place, now 1.9 to 2.6), and rows of one
+    value or with all but three entries at -inf cost no more than others (up to 2.3 times before)."""
+    from paper_2412_10418_amd.binding import cdsl_op_logit_rows
+    g = torch.Generator(device="cuda").manual_seed(V)
+    z = torch.randn((M, V), generator=g, device="cuda") * 3
+    masked = torch.full((M, V), -float("inf"), device="cuda")
+    masked[:, V // 2:V // 2 + 3] = 1.0
+    ids = torch.zeros(M, dtype=torch.int32, device="cuda")
+    us = {n: _us(lambda: cdsl_op_logit_rows(x, ids, kk))
+          for n, x, kk in [("one", z, 1), ("5", z, 5), ("16", z, 16), ("const", torch.ones_like(z), 5), ("masked", masked, 5)]}
+    print(us, flush=True)
+    assert us["16"] < 3.3 * us["one"] and us["const"] < 1.5 * us["5"] and us["masked"] < 1.5 * us["5"]
 
 
 @pytest.mark.parametrize("G,d,V,skew", [(2, 3, 5, 0), (3, 2, 1023, 0), (2, 2, 4099, 0), (2, 2, 9001, 1), (1, 3, 40003, 0),
