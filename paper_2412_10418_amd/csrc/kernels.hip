@@ -571,12 +571,15 @@ __global__ __launch_bounds__(NT) void logit_rows_kernel(LogitArgs a) {
     }
   }
   if (bv == -INFINITY) {
-    // nothing above -inf: the first whole slot with a -inf of the row itself
+    // nothing above -inf: the first slot with a -inf of the row itself (the
+    // row may begin and end inside a slot)
     for (int q = tid; q < rs.slots && bs == kNoId; q += NT) {
       float x[4];
       rs.load(q, x);
       const int id = 4 * q - rs.shift;
-      if (id >= 0 && id + 4 <= a.V && (x[0] == bv || x[1] == bv || x[2] == bv || x[3] == bv)) bs = q;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (x[e] == bv && id + e >= 0 && id + e < a.V) bs = q;
     }
   }
   const int dst = a.topk_rows ? a.topk_rows[row] : row;

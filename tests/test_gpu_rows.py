@@ -101,6 +101,24 @@ def test_logit_rows_alignment_ties_and_infinities(M, V, kk):
             assert tl[m, u] == r or abs(tl[m, u] - r) < 2e-5
 
 
+@pytest.mark.parametrize("V", [1, 2, 3, 5, 63, 1023, 4098, 20001])
+@pytest.mark.parametrize("kk", [0, 1, 2, 16])
+def test_logit_rows_without_a_finite_entry(V, kk):
+    """Rows at each alignment (they begin and end inside a 16-byte slot) whose entries are all -inf, or NaN up to a
+    place and -inf from there: the lowest ids of the -inf entries, in order."""
+    from paper_2412_10418_amd.binding import cdsl_op_logit_rows
+    z = np.full((8, V), -np.inf, np.float32)
+    for m in range(4, 8):
+        z[m, :min(m - 3, V - 1)] = np.nan
+    kk = min(kk, V)
+    _, amax, tk, _ = (t.cpu().numpy() for t in
+                      cdsl_op_logit_rows(torch.from_numpy(z).cuda(), torch.zeros(8, dtype=torch.int32).cuda(), kk))
+    for m in range(8):
+        want = _order(z[m], max(kk, 1))
+        assert amax[m] == want[0]
+        assert list(tk[m][:min(kk, len(want))]) == list(want[:kk])
+
+
 @pytest.mark.parametrize("V", [20001, 128256])
 def test_logit_rows_with_the_best_entries_in_few_threads(V):
     """Every entry of one slot of four in 32 (the slots of one group of threads) lies above all others: more entries
