@@ -43,13 +43,15 @@ int cdsl_op_gemm(const void* A, const void* B, float* C, int32_t M, int32_t N,
  * same kernels, with the workspace taken from a scratch array the library
  * holds in device memory, CDSL_OP_GEMM_STATIC_BYTES (64 MiB) on each GPU it
  * runs on, until the process ends.  No allocation happens in the call.
- * Shapes whose cdsl_op_gemm_workspace exceeds that size are refused with
- * ERANGE (for bf16 weights: 4 M K bytes of planes plus 4 S M N bytes of S
- * K-split planes; e.g. M = 800 at N = K = 4096 needs 52 MB).  Every call on
- * one GPU shares that GPU's array: calls that overlap on one GPU (two
- * streams, two threads) race and must be serialised by the caller.  The
- * first call on a device looks up that device's copy of the array.  Errors:
- * EINVAL, ERANGE, EDEVICE. */
+ * Shapes whose hi / lo planes of A (4 M K bytes, bf16 weights only) exceed
+ * that size are refused with ERANGE.  The planes of a K split get what is
+ * left: results are cdsl_op_gemm's, bit for bit, where cdsl_op_gemm_workspace
+ * fits (e.g. M = 500, N = 22016, K = 4096: 8 MB), and otherwise those of a
+ * smaller split, as accurate (e.g. 716 x 2830 x 12000, whose own split needs
+ * 87 MB).  Every call on one GPU shares that GPU's array: calls that overlap
+ * on one GPU (two streams, two threads) race and must be serialised by the
+ * caller.  The first call on a device looks up that device's copy of the
+ * array.  Errors: EINVAL, ERANGE, EDEVICE. */
 #define CDSL_OP_GEMM_STATIC_BYTES (64u << 20)
 int cdsl_op_gemm_static(const void* A, const void* B, float* C, int32_t M,
                         int32_t N, int32_t K, int32_t dtype, int32_t epilogue,

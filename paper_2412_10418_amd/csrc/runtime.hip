@@ -1696,42 +1696,6 @@ int op_gemm(const void* A, const void* B, float* C, int32_t M, int32_t N, int32_
   return CDSL_OK;
 }
 
-// The bytes that cdsl_op_gemm_static's limit is about: the planes of A and
-// those of a K split that fills the chip with tiles of 160 x 256 (more than
-// 128 rows) or of 64 or 128 columns.  It says which shapes are taken; the
-// split that runs is the plan's, within the scratch.
-size_t static_need(int M, int N, int K, int dtype) {
-  if (M <= 0 || N <= 0 || K <= 0) return 0;
-  if (dtype != CDSL_BF16) return 0;
-  int s = 1;
-  if (M <= 128 && K % 64 == 0) {
-    const int nst = K / 64;
-    const bool wide = (N + 63) / 64 >= 200, two = wide && (N + 127) / 128 >= 200;
-    const int ring = wide && !two ? 8 : 4, tiles = two ? (N + 127) / 128 : (N + 63) / 64;
-    s = std::max(1, std::min(wide ? 1 : (256 + tiles - 1) / tiles, nst / ring));
-    int per = (nst + s - 1) / s;
-    if (nst >= ring) per = (per + ring - 1) / ring * ring;
-    s = (nst + per - 1) / per;
-  } else {
-    const int tiles = ((M + 159) / 160) * ((N + 255) / 256), nk = K / (K % 64 ? 32 : 64);
-    double best = 1e300;
-    for (int c = 1; c <= 32 && c <= std::max(1, nk / 2); ++c) {
-      const int per = (nk + c - 1) / c;
-      const double rounds = (double)((tiles * c + 255) / 256);
-      const double planes = c > 1 ? (c + 1.0) * M * N * 4.0 / 5e12 / 2e-6 : 0.0;
-      const double t = (rounds * (per + 2.0) + planes) * (c > 1 ? 1.05 : 1.0);
-      if (t < best - 1e-9) {
-        best = t;
-        s = c;
-      }
-    }
-    const int per = (nk + s - 1) / s;
-    s = (nk + per - 1) / per;
-  }
-  const size_t split = s > 1 ? ((size_t)s * M * N * sizeof(float) + 255) & ~(size_t)255 : 0;
-  return op_planes_bytes(M, K, dtype) + split;
-}
-
 int op_gemm_check(const void* A, const void* B, const float* C, int32_t M, int32_t N, int32_t K, int32_t dtype,
                   int32_t epilogue) {
   if (!A || !B || !C) return fail(nullptr, CDSL_EINVAL, "null argument");
@@ -1769,10 +1733,11 @@ int cdsl_op_gemm_static(const void* A, const void* B, float* C, int32_t M, int32
                         int32_t epilogue, void* stream) {
   const int rc = op_gemm_check(A, B, C, M, N, K, dtype, epilogue);
   if (rc != CDSL_OK) return rc;
-  const size_t need = static_need(M, N, K, dtype);
-  if (need > CDSL_OP_GEMM_STATIC_BYTES)
+  // the K split takes what the planes of A leave, so only they can be too much
+  const size_t planes = op_planes_bytes(M, K, dtype);
+  if (planes > CDSL_OP_GEMM_STATIC_BYTES)
     return fail(nullptr, CDSL_ERANGE,
-                "shape needs " + std::to_string(need) + " bytes of workspace; the static scratch holds " +
+                "the hi / lo planes of A need " + std::to_string(planes) + " bytes; the static scratch holds " +
                     std::to_string((size_t)CDSL_OP_GEMM_STATIC_BYTES));
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
@@ -1790,7 +1755,7 @@ int cdsl_op_gemm_static(const void* A, const void* B, float* C, int32_t M, int32
     ws = g_scratch_dev[dev];
   }
   return op_gemm(A, B, C, M, N, K, dtype, epilogue, ws, CDSL_OP_GEMM_STATIC_BYTES, stream,
-                 CDSL_OP_GEMM_STATIC_BYTES - op_planes_bytes(M, K, dtype));
+                 CDSL_OP_GEMM_STATIC_BYTES - planes);
 }
 
 int cdsl_op_logit_rows(const float* logits, int32_t M, int32_t V, const int32_t* gather, int32_t kk, float* lp,

@@ -1,8 +1,8 @@
 """cdsl_op_gemm_static (the projection for callers that cannot allocate)
 through the C ABI: two calls in a row, the second smaller, each equal to
 cdsl_op_gemm with a caller workspace (the same kernels, so bitwise) and
-within fp32 accuracy of float64; a shape whose workspace exceeds the static
-scratch is refused."""
+within fp32 accuracy of float64; shapes whose workspace fits are taken, one
+whose planes of A alone exceed the static scratch is refused."""
 import ctypes
 
 import numpy as np
@@ -46,6 +46,19 @@ def test_static_scratch_gemm_matches_the_workspace_entry_point():
         exact = a.astype(np.float64) @ b.astype(np.float64).T
         err = np.max(np.abs(got.cpu().numpy() - exact)) / max(1.0, np.max(np.abs(exact)))
         assert err < 5e-6, err
+
+
+@pytest.mark.parametrize("M,N,K", [(426, 12288, 4096), (833, 4096, 11008), (500, 22016, 4096)])
+def test_static_scratch_takes_every_shape_whose_workspace_fits(M, N, K):
+    """These run with little or no K split, so their workspace is far below the scratch's size."""
+    from paper_2412_10418_amd import binding as bd
+    assert bd.lib().cdsl_op_gemm_workspace(M, N, K, bd.CDSL_BF16) <= (64 << 20)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    ta = torch.randn((M, K), generator=g, device="cuda")
+    tb = (torch.randn((N, K), generator=g, device="cuda") * 0.02).bfloat16()
+    rc, got = _static(ta, tb, M, N, K)
+    assert rc == bd.CDSL_OK, bd.lib().cdsl_last_error(None)
+    assert torch.equal(got, bd.cdsl_op_gemm(ta, tb))
 
 
 def test_static_scratch_refuses_a_shape_beyond_its_size():
