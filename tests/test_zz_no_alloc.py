@@ -1,5 +1,5 @@
 """cdsl_op_gemm_static (the projection for callers that cannot allocate)
-through the C ABI: two calls in a row, the second smaller, each equal to
+through the C ABI: calls in a row, with and without a K split, each equal to
 cdsl_op_gemm with a caller workspace (the same kernels, so bitwise) and
 within fp32 accuracy of float64; shapes whose workspace fits are taken, one
 whose planes of A alone exceed the static scratch is refused."""
@@ -32,11 +32,15 @@ def _static(ta, tb, M, N, K):
 
 def test_static_scratch_gemm_matches_the_workspace_entry_point():
     from paper_2412_10418_amd import binding as bd
-    # the verification's o-projection (K split over 3 planes: 52 MB of
-    # workspace), then a smaller rollout-sized call on the same scratch
-    for M, N, K in [(800, 4096, 4096), (80, 3072, 2048)]:
+    # an unsplit call, one whose K is split over several planes (48 MB of
+    # workspace), then smaller ones on the same scratch, split and not
+    for M, N, K, split in [(800, 4096, 4096, False), (400, 4096, 11008, True), (80, 2048, 8192, True),
+                           (80, 3072, 2048, False)]:
         print(f"static-scratch gemm {M}x{N}x{K}", flush=True)
-        assert bd.lib().cdsl_op_gemm_workspace(M, N, K, bd.CDSL_BF16) <= (64 << 20)
+        need = bd.lib().cdsl_op_gemm_workspace(M, N, K, bd.CDSL_BF16)
+        assert need <= (64 << 20)
+        if split:   # the hi / lo planes of A and at least two planes of the product
+            assert need >= 4 * M * K + 8 * M * N
         a, b, ta, tb = _operands(M, N, K, 31)
         ref = bd.cdsl_op_gemm(ta, tb)
         rc, got = _static(ta, tb, M, N, K)
