@@ -12,7 +12,7 @@ import pytest
 import torch
 
 import cdsl_inputs as ci
-from cdsl_harness import make_engine, make_setup
+from cdsl_harness import assert_full_or_tie, make_engine, make_setup, run_and_compare
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +64,18 @@ def test_rotary_epilogue_matches_the_rotary_kernel(monkeypatch, case):
         assert len({la[b].tobytes() for b in range(nb)}) > 1
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("nb,L,k,d", [(1, 16, 2, 3), (2, 17, 2, 17), (1, 35, 1, 20), (2, 50, 2, 16)])
+def test_split_projections_over_several_blocks_of_slots(nb, L, k, d):
+    """Few rows: the target's q/k/v projection is split in K, and the rotary kernel that folds its planes writes V runs
+    over up to four blocks of 16 slots (whole and partial ones; prompts, and beams of up to 20 rows), against the
+    oracle with the harness's tolerance."""
+    s = make_setup("small", draft=GQA_DRAFT, target=GQA_TARGET, batch=nb, prompt_len=L, k=k, d=d)
+    make_engine(s, B=nb, max_steps=3, k=k, d=d)
+    try:
+        st, reps = run_and_compare(s, B=nb, steps=2, check_prompts=list(range(nb)), k=k, d=d)
+        assert_full_or_tie(reps, 2)
+        st.prefix.free()
+    finally:
+        s.engine.close()
