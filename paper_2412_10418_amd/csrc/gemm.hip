@@ -223,46 +223,55 @@ __global__ __launch_bounds__(256) void split_planes8(const float* __restrict__ x
 // ---------------------------------------------------------------------------
 // plan
 // ---------------------------------------------------------------------------
-// What a configuration's workgroups cost, fitted to 16 thousand timings on
-// MI355X (1 to 4096 rows, the projections and heads of 1B to 7B models, every
-// split; weights from HBM), in us.  occ workgroups share a CU, so a round
-// holds 256 * occ of them; a round of n workgroups of `per` stages takes
-//   round + per * sqrt(lone^2 + (full * n / (256 * occ))^2 + (fill * c)^2),
-// lone the stage time of a workgroup by itself (latency), full the growth
-// when every slot is taken (matrix cores shared, lower clocks), c the time of
-// the round's copies into LDS at 12.5 TB/s (rows past M are not read).  Over
-// those shapes the model's choice is on average 2% slower than the best
-// measured (configuration, split) pair; these eleven configurations together
-// are within 1% of the best of the 26 that were timed.
+// What a configuration's workgroups cost, fitted to 26 thousand timings on
+// MI355X (1 to 4096 rows, 33 pairs of N and K, every split; weights from HBM),
+// in us.  occ workgroups share a CU (DenseCfg::OCC), so a round holds 256 * occ
+// of them; a round of n workgroups of `per` stages takes
+//   round + per * sqrt(lone^2 + (full * (busy - 1))^2 + (fill * c)^2),
+// lone the stage time of a workgroup by itself (latency), busy the workgroups
+// of the fullest CU (a round lasts as long as that CU: 282 workgroups of 64 x
+// 64 take what 512 take), c the time of the round's copies into LDS at 12.5
+// TB/s (rows past M are not read).  The weights' trip from HBM adds as the
+// root of squares, so that shapes that wait for it still differ.  A split
+// costs the writes of its planes, and the launch of its reduce (2.1 to 2.5 us
+// measured, and 123 MB of planes in 20) or what the consumer takes longer
+// (RMSNorm of 80 rows of 2048: 2.8 us without planes, 3.7 with two to eight; of
+// 800 rows of 4096 6.0, 13.3 and 23.9: planes beyond the caches).  Over those
+// shapes the model's choice is on average 2% slower than the best measured pair
+// (worst: 29%); a table that counted three workgroups per CU where two ran, that
+// charged 4.5 us for a reduce and that took the load of all CUs for that of each
+// was 6 to 9% slower (1 x 2048 x 2048 with its reduce 10.1 us unsplit, 6.4 in
+// eight splits).
 //
 // Measured with them (product alone, us; the earlier pair of kernels, one
 // for up to 128 rows with weights in registers and one with 160 x 256 tiles
-// staged through registers, in brackets): 800 x 12288 x 4096 126 (160), 800 x
-// 22016 x 4096 239 (271), 800 x 4096 x 4096 54 (60 and its split planes),
-// 4096 x 22016 x 4096 1067 (1440, 692 TFLOP/s of product), 160 x 16384 x 2048
-// 31 (43), 80 x 22016 x 4096 55 (81), 80 x 16384 x 2048 23 (27), 80 x 32000 x
-// 2048 36 (45), 16 x 22016 x 4096 41 (49), 16 x 8192 x 1024 6.9 (9.9).
+// staged through registers, in brackets): 800 x 12288 x 4096 117 (160), 800 x
+// 22016 x 4096 230 (271), 4096 x 22016 x 4096 1044 (1440, 708 TFLOP/s of
+// product), 160 x 16384 x 2048 27 (43), 80 x 22016 x 4096 51 (81), 80 x 16384 x
+// 2048 21 (27), 80 x 32000 x 2048 37 (45), 16 x 22016 x 4096 40 (49), 16 x 8192
+// x 1024 5.7 (9.9).
 #define CFG_SHAPE(I, WM, WN, TM, TN, P) {WM * TM * 16, WN * TN * 16},
 constexpr int kShape[kGemmCfgs][2] = {CDSL_GEMM_CFGS(CFG_SHAPE)};
 #undef CFG_SHAPE
+#define CFG_OCC(I, ...) DenseCfg<__VA_ARGS__>::OCC,
+constexpr int kOcc[kGemmCfgs] = {CDSL_GEMM_CFGS(CFG_OCC)};
+#undef CFG_OCC
 constexpr struct {
-  int occ;
   float start, round, lone, full, fill;
 } kCost[] = {
-    {1, 6.8f, 6.7f, 1.51f, 0.74f, 1.29f},   // 256 x 256
-    {1, 5.7f, 5.2f, 1.04f, 0.68f, 1.08f},   // 160 x 256
-    {1, 5.4f, 4.5f, 0.86f, 0.86f, 0.82f},   // 128 x 256
-    {1, 5.0f, 4.1f, 0.58f, 0.47f, 0.73f},   // 160 x 128
-    {1, 4.5f, 3.6f, 0.47f, 0.46f, 0.63f},   // 128 x 128
-    {1, 4.6f, 3.4f, 0.54f, 0.76f, 0.00f},   // 64 x 256
-    {1, 3.6f, 2.4f, 0.37f, 0.23f, 0.62f},   // 64 x 128
-    {2, 3.6f, 1.6f, 0.23f, 0.47f, 0.53f},   // 64 x 64
-    {2, 3.0f, 1.3f, 0.24f, 0.35f, 0.87f},   // 48 x 64
-    {3, 3.2f, 0.8f, 0.18f, 0.23f, 0.95f},   // 32 x 64
-    {3, 3.1f, 0.5f, 0.18f, 0.26f, 0.97f},   // 16 x 64
+    {4.7f, 3.1f, 1.94f, 0.00f, 0.89f},   // 256 x 256
+    {3.8f, 3.1f, 1.32f, 0.00f, 0.79f},   // 160 x 256
+    {3.7f, 2.8f, 1.03f, 0.00f, 0.78f},   // 128 x 256
+    {2.8f, 3.3f, 0.70f, 0.00f, 0.67f},   // 160 x 128
+    {2.4f, 3.0f, 0.57f, 0.00f, 0.64f},   // 128 x 128
+    {2.3f, 2.8f, 0.65f, 0.00f, 0.55f},   // 64 x 256
+    {1.9f, 1.8f, 0.45f, 0.00f, 0.50f},   // 64 x 128
+    {2.1f, 1.2f, 0.32f, 0.48f, 0.39f},   // 64 x 64
+    {1.8f, 1.3f, 0.30f, 0.47f, 0.42f},   // 48 x 64
+    {1.6f, 1.2f, 0.24f, 0.41f, 0.29f},   // 32 x 64
+    {2.3f, 0.4f, 0.20f, 0.31f, 0.26f},   // 16 x 64
 };
 static_assert(sizeof(kCost) / sizeof(kCost[0]) == kGemmCfgs, "a cost per configuration");
-constexpr double kPlaneRate = 5e6;   // bytes per us of split planes (written, then read by the fold)
 
 struct Plan {
   int kind;          // 0 dense, 1 skinny, 2 f32
@@ -280,12 +289,20 @@ enum SplitUse { kFold = 0, kReduce = 1, kNone = 2 };
 
 double cfg_us(int cfg, int rows, int tiles, int splits, int per) {
   const auto& c = kCost[cfg];
-  const int n = tiles * splits, cap = 256 * c.occ, full = n / cap, rem = n % cap;
+  const int n = tiles * splits, cap = 256 * kOcc[cfg], full = n / cap, rem = n % cap;
   auto round = [&](int k) {
-    const double f = c.full * k / cap, m = c.fill * (2 * rows + kShape[cfg][1]) * (2.0 * DKC) * k / 12.5e6;
+    const double f = c.full * ((k + 255) / 256 - 1), m = c.fill * (2 * rows + kShape[cfg][1]) * (2.0 * DKC) * k / 12.5e6;
     return c.round + per * sqrt((double)c.lone * c.lone + f * f + m * m);
   };
   return c.start + full * round(cap) + (rem ? round(rem) : 0.0);
+}
+
+// What ks planes of `plane` bytes cost: their writes, then the reduce launch or
+// what their consumer takes longer.
+double split_us(SplitUse use, int ks, double plane) {
+  if (ks == 1) return 0.0;
+  const double b = (ks + 1) * plane, write = ks * plane / 8.3e6;
+  return write + (use == kReduce ? 2.3 + b / 8e6 : 1.0 + b / 16e6 + std::max(0.0, b - 32e6) / 10e6);
 }
 
 // The plan of a shape: a pure function of its arguments.  hd > 0: only
@@ -297,7 +314,7 @@ Plan search_plan(int M, int N, int K, SplitUse use, int hd, size_t max_ws) {
   p.kind = M <= 128 ? 1 : 0;
   const int M16 = (M + 15) / 16 * 16, nk = (K - 1) / DKC + 1;
   // weights once from HBM, whatever the tiles
-  const double stream = 3.0 + (double)N * K * 2.0 / 4.9e6;
+  const double stream = 1.2 + (double)N * K * 2.0 / 6.5e6;
   p.us = 1e300;
   for (int c = 0; c < kGemmCfgs; ++c) {
     const int bm = kShape[c][0], bn = kShape[c][1];
@@ -313,10 +330,8 @@ Plan search_plan(int M, int N, int K, SplitUse use, int hd, size_t max_ws) {
       const int per = (nk + s - 1) / s, ks = (nk + per - 1) / per;
       if (ks == last) continue;
       last = ks;
-      const double plane = (double)M16 * N * 4.0;
       if (ks > 1 && ks * ((double)M * N * 4.0) > (double)max_ws) break;
-      double us = std::max(cfg_us(c, M16 / (int)tm, tiles, ks, per), stream);
-      if (ks > 1) us += (use == kReduce ? 4.5 : 2.0) + (ks + 1) * plane / kPlaneRate;
+      const double us = hypot(cfg_us(c, M16 / (int)tm, tiles, ks, per), stream) + split_us(use, ks, (double)M16 * N * 4.0);
       if (us < p.us) {
         p.us = us;
         p.cfg = c;
@@ -376,17 +391,18 @@ int gemm_rowstats_tiles(int M, int N, int K, int dtype) {
 }
 
 // The rotary epilogue needs an unsplit launch of tiles with whole heads.  It
-// takes 3 to 14 us more than the stores' (80 x 3072: 15.7 us in all, against
-// 9.4 split in four and 5.4 for the rotary launch that folds the planes; 800
-// x 12288: 139, against 126 and a launch that reads the 39 MB product), and
-// saves the rotary launch and the product's trip through memory.  So it is
-// taken where the projection is best not split anyway, and where a split
-// (whose planes are in its plan's time) gains less than 2 us.
+// takes 1 to 5 us more than the stores' (up to 16 where rows of a beam do not
+// start at multiples of four slots: 800 rows of ten, 12288 columns), and saves
+// the rotary launch, 3 to 10 us with the product's trip through memory.  So it
+// is taken where the unsplit product costs at most 2.5 us more than the best
+// one with its planes (both by the plan).  Over 111 shapes of 5 models, 8 to 2000
+// rows, that is 1.4% slower on average than always taking the faster (with no
+// such allowance 3.8%): 160 rows of 3072 x 1024 9.9 us against 14.1, 105 of 3072 x
+// 2048 17.0 and 17.3, 160 of 6144 x 2048 21.0 and 22.6, 96 of 6144 x 4096 35 and 24.
 bool gemm_rope_fusable(int M, int N, int K, int dtype, int hd) {
   if (M <= 0 || dtype != 1 || (hd != 64 && hd != 128) || N % hd != 0) return false;
   const Plan f = make_plan(M, N, K, dtype, kNone, hd), s = make_plan(M, N, K, dtype, kFold);
-  if (f.us > 1e200) return false;
-  return f.us <= s.us + (s.ksplit == 1 ? 1.0 + 2.0 * M * (double)N * 4.0 / kPlaneRate : -2.0);
+  return f.us <= s.us + 2.5;
 }
 
 int gemm_check(int M, int N, int K, int dtype) {

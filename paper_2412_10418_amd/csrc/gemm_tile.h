@@ -488,6 +488,11 @@ struct DenseCfg {
   static constexpr int PR = BM / NP;
   static constexpr int TILE = PR * BN * 4;
   static constexpr int LDS = RING + PAD > TILE ? RING + PAD : TILE;
+  // workgroups that share a CU: by LDS and, but for four waves of one or two
+  // 16 x 16 tiles each, by registers (two waves per SIMD)
+  static constexpr int OCC = 160 * 1024 / LDS;
+  static constexpr int WAVES = OCC * NW / 4;   // per SIMD
+  static_assert(WAVES == 2 || (WAVES == 3 && TM * TN <= 2), "the registers of the waves that LDS lets in");
   static_assert(BN / 8 % NW == 0 && LDS <= 160 * 1024 && PR % (TM * 16) == 0, "tile fits");
 };
 
@@ -750,7 +755,8 @@ __device__ __forceinline__ void gemm_bf16(const GemmArgs& a) {
 #define CDSL_GEMM_KERNELS(KERNEL, LAUNCH)                                                                   \
   namespace {                                                                                               \
   template <int WM, int WN, int TM, int TN, int P, int EPI, bool DMA, int KIND>                             \
-  __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 2))) void KERNEL(GemmArgs a) { \
+  __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(                                    \
+      2, DenseCfg<WM, WN, TM, TN, P>::WAVES))) void KERNEL(GemmArgs a) {                                    \
     gemm_bf16<WM, WN, TM, TN, P, EPI, DMA>(a);                                                              \
   }                                                                                                         \
   }                                                                                                         \

@@ -82,3 +82,11 @@ def test_error_paths_without_device(lib):
     assert L.cdsl_op_logit_rows(None, 1, 1, None, 0, None, None, None, None, None) == binding.CDSL_EINVAL
     assert L.cdsl_op_gemm_workspace(80, 3072, 2048, binding.CDSL_BF16) > 0
     assert L.cdsl_op_gemm_workspace(0, 3072, 2048, binding.CDSL_BF16) == 0
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 2048, 2048), (16, 2048, 2048), (32, 3072, 2048), (128, 2048, 2048), (24, 1024, 4096)])
+def test_projections_with_few_tiles_are_split(M, N, K):
+    """Their tiles fill an eighth to a quarter of the CUs, so a K split is faster even with its reduce (1 x 2048 x 2048:
+    6.4 against 10.1 us): the workspace holds the planes of A and at least two of the product."""
+    from paper_2412_10418_amd import binding as bd
+    assert bd.lib().cdsl_op_gemm_workspace(M, N, K, bd.CDSL_BF16) >= 4 * M * K + 2 * 4 * M * N

@@ -32,7 +32,7 @@ def _static(ta, tb, M, N, K):
 
 def test_static_scratch_gemm_matches_the_workspace_entry_point():
     from paper_2412_10418_amd import binding as bd
-    # an unsplit call, one whose K is split over several planes (48 MB of
+    # an unsplit call, one whose K is split over several planes (42 MB of
     # workspace), then smaller ones on the same scratch, split and not
     for M, N, K, split in [(800, 4096, 4096, False), (400, 4096, 11008, True), (80, 2048, 8192, True),
                            (80, 3072, 2048, False)]:
@@ -52,17 +52,21 @@ def test_static_scratch_gemm_matches_the_workspace_entry_point():
         assert err < 5e-6, err
 
 
-@pytest.mark.parametrize("M,N,K", [(426, 12288, 4096), (833, 4096, 11008), (500, 22016, 4096)])
-def test_static_scratch_takes_every_shape_whose_workspace_fits(M, N, K):
-    """These run with little or no K split, so their workspace is far below the scratch's size."""
+@pytest.mark.parametrize("M,N,K", [(426, 12288, 4096), (500, 22016, 4096), (833, 4096, 11008)])
+def test_static_scratch_takes_every_shape_whose_planes_fit(M, N, K):
+    """The first two need no K split, so their workspace is far below the scratch's size; the third's planes of A leave
+    room for a small split only.  Bitwise cdsl_op_gemm's result where its workspace fits, else as accurate (the
+    tolerance of the calls above)."""
     from paper_2412_10418_amd import binding as bd
-    assert bd.lib().cdsl_op_gemm_workspace(M, N, K, bd.CDSL_BF16) <= (64 << 20)
     g = torch.Generator(device="cuda").manual_seed(M)
     ta = torch.randn((M, K), generator=g, device="cuda")
     tb = (torch.randn((N, K), generator=g, device="cuda") * 0.02).bfloat16()
     rc, got = _static(ta, tb, M, N, K)
     assert rc == bd.CDSL_OK, bd.lib().cdsl_last_error(None)
-    assert torch.equal(got, bd.cdsl_op_gemm(ta, tb))
+    if bd.lib().cdsl_op_gemm_workspace(M, N, K, bd.CDSL_BF16) <= (64 << 20):
+        assert torch.equal(got, bd.cdsl_op_gemm(ta, tb))
+    ref = torch.matmul(ta.double(), tb.double().t())
+    assert float((got.double() - ref).abs().max() / ref.abs().max()) < 5e-6
 
 
 def test_static_scratch_refuses_a_shape_beyond_its_size():
