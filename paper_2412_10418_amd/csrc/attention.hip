@@ -13,8 +13,8 @@
 // (hi, lo) planes.  The workgroup first lists the key blocks its rows can
 // see, then streams them in pairs (32 keys) through double-buffered LDS,
 // the next pair's global loads in flight while the current pair is
-// computed.  Per wave: 16 query rows.  Scores are computed transposed, per
-// block of 16 keys,
+// computed.  Per wave: 16 query rows, or two tiles of 16.  Scores are computed
+// transposed, per tile and block of 16 keys,
 //   S^T[16 keys, 16 rows] = K[16, hd] . Q^T[hd, 16]      (MFMA 16x16x32)
 // so that lane (row r, group g) holds keys 4g..4g+3 of both blocks of the
 // pair -- exactly its B fragment of
@@ -678,10 +678,12 @@ AttnPlan attn_plan(const PassDesc& p, int H, int Hkv, int hd, int dtype, int max
   pl.kw = pl.row_tiles <= 2 ? (hd == 64 ? 4 : 2) : 1;
   if (hd == 64 && pl.row_tiles >= 2 && pl.row_tiles <= 4 && (p.nb * Hkv >= 256 || ((nK + 1) / 2 + 3) / 4 > 8)) {
     // eight waves: 2 row tiles x 4 key groups, or 4 x 2; the keys are read
-    // once per (prompt, KV head) instead of once per row tile.  With fewer
-    // than 256 (prompt, KV head) pairs the pass is latency-bound and twice
-    // the workgroups (one per row tile) finish sooner (measured at 16
-    // prompts x 8 KV heads: the eight-wave form cost 0.1 ms more per step)
+    // once per (prompt, KV head) instead of once per row tile.  From 256 pairs
+    // up, or where a workgroup of four waves would take more than eight
+    // iterations (16 prompts x 8 KV heads x 2048 keys: 66 -> 51 us); else the
+    // pass is latency-bound and twice the workgroups (one per row tile) finish
+    // sooner (16 prompts x 8 KV heads x 256 keys: the eight-wave form cost 0.1
+    // ms more per step)
     pl.threads = 512;
     pl.kw = pl.row_tiles == 2 ? 4 : 2;
   } else if (pl.row_tiles > 4) {
