@@ -324,9 +324,22 @@ __device__ __forceinline__ void rope_epilogue(const GemmArgs& a, const f32x4 (&a
 #pragma unroll 1
   for (int p0 = 0; p0 < BM; p0 += PR) {
     if (nrot <= 0) break;
+    // cos and sin of every unit where the accumulators leave the registers
+    // for them; 256 x 256 tiles, whose 128 do not, as a unit is done (prompts of
+    // 4096 rows, 12288 columns: 396 us with 48 registers spilled, now 389)
+    constexpr bool AHEAD = TM * TN <= 20;
     int2 ri[UPT];
-    float4 cs[UPT][4];
+    float4 cs[AHEAD ? UPT : 1][4];
     bool live[UPT];
+    auto load_cs = [&](int w, float4 (&x)[4]) {
+      const int d = (threadIdx.x + NT * w) % C8 * 8;
+      const float* ct = re.cos_t + (long long)ri[w].y * HALF + d;
+      const float* st = re.sin_t + (long long)ri[w].y * HALF + d;
+      x[0] = *(const float4*)ct;
+      x[1] = *(const float4*)(ct + 4);
+      x[2] = *(const float4*)st;
+      x[3] = *(const float4*)(st + 4);
+    };
 #pragma unroll
     for (int w = 0; w < UPT; ++w) {
       const int u = threadIdx.x + NT * w;
@@ -334,16 +347,9 @@ __device__ __forceinline__ void rope_epilogue(const GemmArgs& a, const f32x4 (&a
       live[w] = u < UN && r < rows && hh < nrot;
       ri[w] = rinfo[m0 + min(r, rows - 1)];
     }
+    if constexpr (AHEAD)
 #pragma unroll
-    for (int w = 0; w < UPT; ++w) {
-      const int d = (threadIdx.x + NT * w) % C8 * 8;
-      const float* ct = re.cos_t + (long long)ri[w].y * HALF + d;
-      const float* st = re.sin_t + (long long)ri[w].y * HALF + d;
-      cs[w][0] = *(const float4*)ct;
-      cs[w][1] = *(const float4*)(ct + 4);
-      cs[w][2] = *(const float4*)st;
-      cs[w][3] = *(const float4*)(st + 4);
-    }
+      for (int w = 0; w < UPT; ++w) load_cs(w, cs[w]);
     // the loads above are in flight while the tile goes to LDS (the K
     // stages' buffers are free once every wave has left the K loop)
     __syncthreads();
@@ -367,8 +373,10 @@ __device__ __forceinline__ void rope_epilogue(const GemmArgs& a, const f32x4 (&a
       const float4 x1a = tile4(r, lc), x1b = tile4(r, lc + 4), x2a = tile4(r, lc + HALF), x2b = tile4(r, lc + HALF + 4);
       const float x1[8] = {x1a.x, x1a.y, x1a.z, x1a.w, x1b.x, x1b.y, x1b.z, x1b.w};
       const float x2[8] = {x2a.x, x2a.y, x2a.z, x2a.w, x2b.x, x2b.y, x2b.z, x2b.w};
-      const float c[8] = {cs[w][0].x, cs[w][0].y, cs[w][0].z, cs[w][0].w, cs[w][1].x, cs[w][1].y, cs[w][1].z, cs[w][1].w};
-      const float sn[8] = {cs[w][2].x, cs[w][2].y, cs[w][2].z, cs[w][2].w, cs[w][3].x, cs[w][3].y, cs[w][3].z, cs[w][3].w};
+      if constexpr (!AHEAD) load_cs(w, cs[0]);
+      const float4(&q4)[4] = cs[AHEAD ? w : 0];
+      const float c[8] = {q4[0].x, q4[0].y, q4[0].z, q4[0].w, q4[1].x, q4[1].y, q4[1].z, q4[1].w};
+      const float sn[8] = {q4[2].x, q4[2].y, q4[2].z, q4[2].w, q4[3].x, q4[3].y, q4[3].z, q4[3].w};
       float y1[8], y2[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
